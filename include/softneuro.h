@@ -111,7 +111,8 @@ typedef struct {
   int32_t id;        /* routine id, unique within the layer; ids enumerate
                         the run dtype first, then the other allowed dtypes
                         in sn_dtype order; within a dtype layout-major, then
-                        algorithm, then parameter index                      */
+                        algorithm, then parameter index; parameters appended
+                        later follow in the same order after all of these   */
   int32_t layout;    /* sn_layout                                            */
   int32_t algo;      /* sn_algo                                              */
   int32_t param;     /* routine-parameter index (tile configuration)         */

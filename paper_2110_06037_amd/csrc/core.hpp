@@ -123,6 +123,7 @@ struct Layer {
   std::vector<uint8_t> wproj;
   std::vector<float> bproj;
   std::vector<Routine> routines;
+  int n_base = 0;  // routines before the appended ones (what older cost tables list)
   std::vector<int64_t> cost;  // per routine, ns; -1 = not profiled
   std::vector<ChildNet> child;  // per routine; empty for routines that are not childnets
   std::string signature;      // identical signatures share profiling results
@@ -197,7 +198,8 @@ int graph_add_layer(Graph& g, const sn_layer_desc& d, const int32_t* inputs, int
                     const void* weight, const float* bias);
 // all edges including the one into the auxiliary output layer (id = n_layers())
 std::vector<Edge> all_edges(const Graph& g);
-std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L);
+// n_base (optional): how many of them come before the appended parameters
+std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L, int* n_base = nullptr);
 bool winograd_applicable(const Layer& L, const Shape& in);
 std::string routine_name(const Graph& g, const Layer& L, const Routine& r);
 // the childnet of a routine (empty when the routine is a single kernel

@@ -26,9 +26,11 @@ static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 struct DevLayer {
   void* w[3] = {};      // per dtype: dense [Kp][R][S][C8] | depthwise [R][S][C8] | fc [Kp][C8]
   void* wu[3] = {};     // per dtype: Winograd U [16][Kp][C8]
-  void* wu4[3] = {};    // per dtype: Winograd F(4x4,3x3) U [36][Kp][C8]
+  void* wu4[3] = {};    // fp32: Winograd F(4x4,3x3) U [36][Kp][C8]
   void* wp[3] = {};     // per dtype: projected-shortcut weights [Kp][C2_8]
   void* wcat[3] = {};   // per dtype: 1x1 layer with a projected shortcut, both weights [Kp][C + C2]
+  void* wks[3] = {};    // per dtype: dense / fc weights in the wave-split kernel's order
+  void* wpks[3] = {};   // per dtype: projected-shortcut weights in that order
   float* bias = nullptr;  // [Kp] (with a projected shortcut: the two biases summed)
   float* zbias = nullptr;  // [Kp] zeros (the shortcut's own launch in the two-launch routine)
 };
@@ -170,6 +172,10 @@ void dev_destroy(Graph& g) {
       if (p) (void)hipFree(p);
     for (void* p : d.wcat)
       if (p) (void)hipFree(p);
+    for (void* p : d.wks)
+      if (p) (void)hipFree(p);
+    for (void* p : d.wpks)
+      if (p) (void)hipFree(p);
     if (d.bias) (void)hipFree(d.bias);
     if (d.zbias) (void)hipFree(d.zbias);
   }
@@ -200,6 +206,16 @@ void dev_upload_layer(Graph& g, int id) {
   dl.bias = static_cast<float*>(dev_upload(bias.data(), bias.size() * 4));
   const uint8_t* src = L.weight.data();
   const int R = L.d.r, S = L.d.s;
+  // the order of the wave-split kernel: routine parameters of the 16-bit
+  // types, part of fp32's one implicit-GEMM routine
+  auto upload_ks = [&](const std::vector<uint8_t>& w, int dt) -> void* {
+    if (!(g.opt_algos >> SN_ALGO_IGEMM & 1) || (!g.opt_params && dt != SN_F32)) return nullptr;
+    const size_t row = w.size() / Kp, bytes = k::ksplit_packed_bytes(Kp, row);
+    if (bytes >= size_t(1) << 31) return nullptr;  // beyond the kernel's offsets
+    std::vector<uint8_t> o(bytes);
+    k::ksplit_pack(w.data(), Kp, row, o.data());
+    return dev_upload(o.data(), o.size());
+  };
   for (int dt = 0; dt < 3; ++dt) {
     if (!(g.opt_dtypes >> dt & 1)) continue;
     const int es = dtype_size(dt);
@@ -213,6 +229,7 @@ void dev_upload_layer(Graph& g, int id) {
       for (int kk = 0; kk < K; ++kk)
         for (int c = 0; c < C; ++c) put(&w[((size_t)kk * C8 + c) * es], (size_t)kk * C + c);
       dl.w[dt] = dev_upload(w.data(), w.size());
+      dl.wks[dt] = upload_ks(w, dt);
       continue;
     }
     if (is_depthwise(g, L)) {  // OIHW [C][1][R][S] -> [R][S][C8]
@@ -232,6 +249,7 @@ void dev_upload_layer(Graph& g, int id) {
           for (int s2 = 0; s2 < S; ++s2)
             put(&w[((((size_t)kk * R + r) * S + s2) * C8 + c) * es], (((size_t)kk * C + c) * R + r) * S + s2);
     dl.w[dt] = dev_upload(w.data(), w.size());
+    dl.wks[dt] = upload_ks(w, dt);
     if (L.proj_stride > 0) {  // shortcut [K][C2] -> [Kp][C2_8]
       const int C2 = g.layers[L.inputs[1]].out.c, C28 = round8(C2);
       std::vector<uint8_t> w2((size_t)Kp * C28 * es, 0);
@@ -242,6 +260,7 @@ void dev_upload_layer(Graph& g, int id) {
           else encode(decode(L.wproj.data() + e * ies, g.dtype), dt, &w2[((size_t)kk * C28 + c) * es]);
         }
       dl.wp[dt] = dev_upload(w2.data(), w2.size());
+      dl.wpks[dt] = upload_ks(w2, dt);
       if (R == 1 && S == 1 && C % 64 == 0 && C2 % 64 == 0) {  // the streaming kernel's filter rows
         std::vector<uint8_t> wc((size_t)Kp * (C + C2) * es);
         for (int kk = 0; kk < Kp; ++kk) {
@@ -251,7 +270,7 @@ void dev_upload_layer(Graph& g, int id) {
         dl.wcat[dt] = dev_upload(wc.data(), wc.size());
       }
     }
-    if (winograd_applicable(L, in)) {
+    if (winograd_applicable(L, in) && (g.opt_algos >> SN_ALGO_WINOGRAD & 1)) {
       // U = G g G^T per (k, c), in float64 from the caller's weights, rounded
       // once to the dtype
       static const double G[4][3] = {{1, 0, 0}, {0.5, 0.5, 0.5}, {0.5, -0.5, 0.5}, {0, 0, 1}};
@@ -271,6 +290,7 @@ void dev_upload_layer(Graph& g, int id) {
             }
         }
       dl.wu[dt] = dev_upload(u.data(), u.size());
+      if (dt != SN_F32) continue;  // the F(4x4,3x3) routine runs in fp32 only
       // F(4x4,3x3): G of the Toom-Cook construction on 0, 1, -1, 2, -2, infinity
       static const double G4[6][3] = {{1.0 / 4, 0, 0},
                                       {-1.0 / 6, -1.0 / 6, -1.0 / 6},
@@ -347,6 +367,7 @@ static void launch_layer(const Graph& g, int id, const Routine& r, const void* c
       a.ws = ws;
       a.ws_bytes = ws_bytes;
       a.cnt = g.dev->fixup_cnt;
+      a.wks = dl.wks[dt];
       a.res = L.inputs.size() > 1 ? in[1] : nullptr;
       if (L.proj_stride > 0) {
         a.res = nullptr;
@@ -375,6 +396,7 @@ static void launch_layer(const Graph& g, int id, const Routine& r, const void* c
           a.x2d = ind[1];
           a.w2 = dl.wp[dt];
           a.wcat = dl.wcat[dt];
+          a.w2ks = dl.wpks[dt];
           a.stride2 = L.proj_stride;
           k::conv_igemm(dt, r.param, a, st);
         }
@@ -427,6 +449,7 @@ static void launch_layer(const Graph& g, int id, const Routine& r, const void* c
         a.ws = ws;
         a.ws_bytes = ws_bytes;
         a.cnt = g.dev->fixup_cnt;
+        a.wks = dl.wks[dt];
         k::conv_igemm(dt, r.param, a, st);
       } else {
         k::fc_direct(dt, in[0], xs.n, xs.c, stored_c(xs, r.layout), dl.w[dt], round8(xs.c), dl.bias, out,

@@ -128,7 +128,7 @@ std::string routine_name(const Graph& g, const Layer& L, const Routine& r) {
   return o.str();
 }
 
-std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L) {
+std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L, int* n_base) {
   std::vector<Routine> out;
   if (L.type == SN_LAYER_INPUT) return out;
   const Shape& in = g.layers[L.inputs[0]].out;
@@ -163,7 +163,7 @@ std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L) {
             add(lay, SN_ALGO_DIRECT, 0);
             if (g.opt_algos >> SN_ALGO_IGEMM & 1) {
               const Shape& sc = g.layers[L.inputs[1]].out;
-              for (int p = 0; p < k::igemm_num_params(dt); ++p)
+              for (int p = 0; p < k::igemm_first_appended_param(dt) && dt != SN_F32; ++p)
                 if (k::igemm_param_takes_projection(dt, p, lay, in.n, in.c, in.h, in.w, L.d.r, L.d.s,
                                                     L.d.stride, L.d.pad, L.d.k, sc.c)) {
                   add(lay, SN_ALGO_IGEMM, p);
@@ -181,7 +181,7 @@ std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L) {
           }
           if (g.opt_algos >> SN_ALGO_DIRECT & 1) add(lay, SN_ALGO_DIRECT, 0);
           if (g.opt_algos >> SN_ALGO_IGEMM & 1) {
-            int np = g.opt_params ? k::igemm_num_params(dt) : 1;
+            int np = g.opt_params ? k::igemm_first_appended_param(dt) : 1;
             for (int p = 0; p < np; ++p)
               if (k::igemm_param_valid(dt, p, lay, in.n, in.c, in.h, in.w, L.d.r, L.d.s, L.d.stride,
                                        L.d.pad, L.d.k) &&
@@ -201,7 +201,7 @@ std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L) {
         case SN_LAYER_FC:
           add(lay, SN_ALGO_DIRECT, 0);
           if (g.opt_algos >> SN_ALGO_IGEMM & 1) {  // the dense childnet: a 1x1 convolution
-            int np = g.opt_params ? k::igemm_num_params(dt) : 1;
+            int np = g.opt_params ? k::igemm_first_appended_param(dt) : 1;
             for (int p = 0; p < np; ++p)
               if (k::igemm_param_valid(dt, p, lay, in.n, in.c, 1, 1, 1, 1, 1, 0, L.d.k))
                 add(lay, SN_ALGO_IGEMM, p);
@@ -212,11 +212,36 @@ std::vector<Routine> enumerate_routines(const Graph& g, const Layer& L) {
       }
     }
   }
+  // the appended parameters, after every routine of every layout and dtype
+  if (n_base) *n_base = (int)out.size();
+  const bool dense = L.type == SN_LAYER_FC || (L.type == SN_LAYER_CONV2D && !is_depthwise(L, in));
+  if (dense && g.opt_params && (g.opt_algos >> SN_ALGO_IGEMM & 1)) {
+    const bool fc = L.type == SN_LAYER_FC;
+    const int r = fc ? 1 : L.d.r, s = fc ? 1 : L.d.s, stride = fc ? 1 : L.d.stride, pad = fc ? 0 : L.d.pad;
+    for (int d : dts) {
+      dt = d;
+      for (int lay = 0; lay < SN_NUM_LAYOUTS; ++lay) {
+        if (!(g.opt_layouts >> lay & 1)) continue;
+        // fp32 projected shortcuts: the one fp32 parameter, appended too
+        const int first = dt == SN_F32 && L.proj_stride > 0 ? 0 : k::igemm_first_appended_param(dt);
+        for (int p = first; p < k::igemm_num_params(dt); ++p)
+          if (L.proj_stride > 0
+                  ? k::igemm_param_takes_projection(dt, p, lay, in.n, in.c, in.h, in.w, r, s, stride, pad, L.d.k,
+                                                    g.layers[L.inputs[1]].out.c)
+                  : k::igemm_param_valid(dt, p, lay, in.n, in.c, in.h, in.w, r, s, stride, pad, L.d.k) &&
+                        (residual == 0 || k::igemm_param_takes_residual(dt, p, lay, L.d.k)))
+            add(lay, SN_ALGO_IGEMM, p);
+      }
+    }
+  }
   if (g.opt_ws_limit >= 0) {
     // memory-restricted selection: only routines within the workspace limit
     std::vector<Routine> kept;
+    const int base = n_base ? *n_base : 0;
+    if (n_base) *n_base = 0;
     for (const Routine& r : out)
       if ((int64_t)routine_ws_bytes(g, L, r) <= g.opt_ws_limit) {
+        if (n_base && r.id < base) ++*n_base;
         kept.push_back(r);
         kept.back().id = (int)kept.size() - 1;
       }
@@ -344,7 +369,7 @@ static int add_layer_impl(Graph& g, const sn_layer_desc& d, const int32_t* input
     if (sc_bias) std::memcpy(L.bproj.data(), sc_bias, sizeof(float) * out.c);
   }
   L.signature = signature(g, L);
-  L.routines = enumerate_routines(g, L);  // (may refuse the layer: the workspace limit)
+  L.routines = enumerate_routines(g, L, &L.n_base);  // (may refuse the layer: the workspace limit)
   g.layers.push_back(std::move(L));
   Layer& ref = g.layers.back();
   ref.cost.assign(ref.routines.size(), -1);

@@ -221,7 +221,9 @@ void costs_from_json(Graph& g, const char* json) {
     if (jl.at("id").as_int() != i) fail(SN_E_INVALID, "layers must be listed in id order");
     const auto& rts = jl.at("routines").as_arr();
     const Layer& L = g.layers[i];
-    if (rts.size() != L.routines.size())
+    // a table written before the appended routines existed lists the others
+    // only: the appended ones then stay without a time (never selected)
+    if (rts.size() != L.routines.size() && !(L.n_base > 0 && (int)rts.size() == L.n_base))
       fail(SN_E_INVALID, "layer " + std::to_string(i) + ": routine count differs");
     for (size_t r = 0; r < rts.size(); ++r) {
       const Routine& R = L.routines[r];
@@ -252,6 +254,10 @@ void costs_from_json(Graph& g, const char* json) {
       }
       cost[i].push_back(ns);
       child[i].push_back(c);
+    }
+    for (size_t r = rts.size(); r < L.routines.size(); ++r) {
+      cost[i].push_back(-1);
+      child[i].push_back(L.child[r]);
     }
   }
   for (int i = 0; i < g.n_layers(); ++i)

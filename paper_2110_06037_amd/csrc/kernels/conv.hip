@@ -19,6 +19,21 @@ int igemm_num_params(int dtype) {
   return dtype == 0 ? (int)(sizeof(kIg32) / sizeof(kIg32[0])) : (int)(sizeof(kIg16) / sizeof(kIg16[0]));
 }
 
+int igemm_first_appended_param(int dtype) {
+  int p = 0;
+  while (p < igemm_num_params(dtype) && (dtype == 0 || kIg16[p].dma != 5)) ++p;
+  return p;
+}
+
+// A wave-split tile is offered up to 2048 workgroups (eight rounds of the 256
+// CUs): past that the launch is bound by the L2-to-register path and the LDS
+// tiles were faster at every size measured, while timing it (500 us for the
+// 16 x 16 tile on a 64-channel 3x3 layer at 32 x 56 x 56) only delays tuning.
+static bool ksplit_fills(int n, int h, int w, int r, int s, int stride, int pad, int k, int bm, int bn) {
+  const long long m = (long long)n * ((h + 2 * pad - r) / stride + 1) * ((w + 2 * pad - s) / stride + 1);
+  return ((m + bm - 1) / bm) * ((k + bn - 1) / bn) <= 2048;
+}
+
 // A configuration whose tile rows do not divide the 256 threads needs the
 // 8-channel vector loader (NHWC with C % 8 == 0, or NC8HW8).
 bool igemm_param_valid(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
@@ -31,6 +46,9 @@ bool igemm_param_valid(int dtype, int param, int layout, int n, int c, int h, in
                             g.pc.ra);
   if (g.dma == 3) return smallc_applicable(layout, c, h, w, r, s, stride, pad, n, k, g.bm / 16, g.ppx, g.gmax);
   if (g.dma == 4) return stream1x1_applicable(layout, c, c, n, h, w, r, s, stride, pad, k, g.bk);
+  if (g.dma == 5)
+    return ksplit_fills(n, h, w, r, s, stride, pad, k, g.bm, g.bn) &&
+           ksplit_applicable(dtype, layout, n, c, h, w, r, s, stride, pad, k, 0);
   if (g.dma) {
     // fp32 index division and 32-bit byte offsets bound the output size
     const long long p = (h + 2 * pad - r) / stride + 1, q = (w + 2 * pad - s) / stride + 1;
@@ -43,12 +61,15 @@ bool igemm_param_valid(int dtype, int param, int layout, int n, int c, int h, in
 bool igemm_param_takes_residual(int dtype, int param, int layout, int k) {
   if (param < 0 || param >= igemm_num_params(dtype)) return false;
   const IgCfg& g = dtype == 0 ? kIg32[param] : kIg16[param];
-  return g.dma == 0 || (g.dma == 1 && (layout == NC8 || k % 8 == 0)) || (g.dma == 4 && layout == NHWC && k % 8 == 0);
+  return g.dma == 0 || g.dma == 5 || (g.dma == 1 && (layout == NC8 || k % 8 == 0)) || (g.dma == 4 && layout == NHWC && k % 8 == 0);
 }
 
 bool igemm_param_takes_projection(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
                                   int stride, int pad, int k, int c2) {
-  if (dtype == 0 || param < 0 || param >= igemm_num_params(dtype)) return false;
+  if (param < 0 || param >= igemm_num_params(dtype)) return false;
+  if (dtype == 0 || kIg16[param].dma == 5)  // the wave-split kernel
+    return (dtype == 0 || ksplit_fills(n, h, w, r, s, stride, pad, k, kIg16[param].bm, kIg16[param].bn)) &&
+           ksplit_applicable(dtype, layout, n, c, h, w, r, s, stride, pad, k, c2);
   if (kIg16[param].dma == 4)  // the streaming 1x1 kernel: both inputs' slabs in one reduction
     return stream1x1_takes_projection(layout, c, c, n, h, w, r, s, stride, pad, k, c2, kIg16[param].bk);
   if (!igemm_param_valid(dtype, param, layout, n, c, h, w, r, s, stride, pad, k)) return false;

@@ -1027,7 +1027,8 @@ struct IgCfg {
                               // the last workgroup of each tile (LDS-DMA kernel only);
                               // pf: prefetch depth (register staging sets)
   int dma = 0, wm = 2, st = 2;  // 1: LDS-DMA kernel, 2: 3x3 patch kernel (bm = 16 * row blocks),
-                                // 3: small-channel kernel, 4: streaming 1x1 kernel (C = bk);
+                                // 3: small-channel kernel, 4: streaming 1x1 kernel (C = bk),
+                                // 5: wave-split kernel;
                                 // wave rows WM (of 4 waves), LDS stages ST
   int ppx = 0;                  // small-channel kernel: patch capacity in pixels
   PatchCfg pc{};                // patch kernel tile
@@ -1107,11 +1108,12 @@ static const IgCfg kIg16[] = {
 #define SN_STREAM_IG(CC, BM, BN, WM, PD) {BM, BN, CC, 0, PD, 4, WM, 2},
     STREAM_OCC2_CONFIGS(SN_STREAM_IG)
 #undef SN_STREAM_IG
+    // wave-split kernel (the first appended parameter, see igemm_first_appended_param)
+#define SN_KSPLIT_IG(FM, FN, NW, D) {16 * FM, 16 * FN, 32, 0, D, 5, 1, 1, 0, {}, NW},
+    KSPLIT_CONFIGS(SN_KSPLIT_IG)
+#undef SN_KSPLIT_IG
 };
 static const IgCfg kIg32[] = {{64, 64, 32, 0, 2}};
-
-
-
 
 static IgCfg ig_cfg(int dtype, int param) {
   check(param >= 0 && param < igemm_num_params(dtype), "unknown implicit-GEMM parameter");
@@ -1369,6 +1371,24 @@ static void igemm_run(const IgCfg& cfg, IgArgs& a, const ConvArgs& c, hipStream_
 template <typename T>
 static void igemm_dispatch(int dtype, int param, const ConvArgs& c, hipStream_t st) {
   const IgCfg cfg = ig_cfg(dtype, param);
+  if (cfg.dma == 5) {  // takes residuals and projected shortcuts wherever it applies
+    check(!c.res || !c.x2, "a projected shortcut replaces the residual");
+    conv_ksplit(dtype, cfg.bm / 16, cfg.bn / 16, cfg.nw, c, st);
+    return;
+  }
+  if constexpr (std::is_same<T, float>::value) {
+    // fp32 has one parameter; the tile follows from the size
+    if (c.wks && ksplit_applicable(dtype, c.xd.layout, c.xd.n, c.xd.c, c.xd.h, c.xd.w, c.r, c.s, c.stride, c.pad,
+                                   c.yd.c, c.x2 ? c.x2d.c : 0)) {
+      const int t = ksplit_pick_f32((long long)c.yd.n * c.yd.h * c.yd.w, c.yd.c,
+                                    (long long)c.r * c.s * c.xd.c + (c.x2 ? c.x2d.c : 0), !c.x2);
+      if (t) {
+        check(!c.res || !c.x2, "a projected shortcut replaces the residual");
+        conv_ksplit(dtype, t / 8, t % 8, 8, c, st);
+        return;
+      }
+    }
+  }
   check(!c.res || cfg.dma == 0 || ((cfg.dma == 1 || cfg.dma == 4) && (c.yd.layout == NC8 || c.yd.cs % 8 == 0)),
         "this tile configuration takes no residual");
   check(!c.x2 || cfg.dma == 4 ||

@@ -74,6 +74,8 @@ struct ConvArgs {
   int stride2 = 1;
   const void* wcat = nullptr;  // 1x1 convolution with a projected shortcut: both weights,
                                // rows [Kp][C8 + C2_8] (the streaming kernel's filter)
+  const void* wks = nullptr;   // w and w2 in the wave-split kernel's order (ksplit_pack)
+  const void* w2ks = nullptr;
 };
 
 void conv_direct(int dtype, const ConvArgs& a, hipStream_t st);
@@ -81,6 +83,9 @@ void conv_direct(int dtype, const ConvArgs& a, hipStream_t st);
 // Parameters that split the reduction need a workspace of igemm_ws_bytes.
 void conv_igemm(int dtype, int param, const ConvArgs& a, hipStream_t st);
 int igemm_num_params(int dtype);
+// parameters from this one on are listed after all other routines of a
+// layer, so that routine ids stored before they existed keep their meaning
+int igemm_first_appended_param(int dtype);
 // whether the tile configuration adds a residual in its epilogue (for an
 // output of k channels in the layout)
 bool igemm_param_takes_residual(int dtype, int param, int layout, int k);
@@ -192,6 +197,29 @@ bool stream1x1_takes_projection(int layout, int c, int cs, int n, int h, int w, 
                                 int k, int c2, int cc);
 // occ: workgroups per CU the persistent grid and the LDS are sized for
 void conv1x1_stream(int dtype, int cc, int bm, int bn, int pd, const ConvArgs& a, hipStream_t st, int occ = 1);
+// Implicit GEMM with the reduction split over a workgroup's waves, for launches
+// bound by latency (see conv_ksplit.hip; NHWC with C % 8 == 0 or NC8HW8, every
+// type; c2 > 0: with a projected shortcut of c2 channels).  Instantiated
+// tiles (FM, FN, NW, D): 16 FM pixels x 16 FN channels, NW waves, D reduction
+// steps in flight per wave; in 16-bit types each is one implicit-GEMM routine
+// parameter, in fp32 the one routine takes a tile by size (ksplit_pick_f32).
+#define KSPLIT_CONFIGS(X) \
+  X(1, 1, 8, 6)           \
+  X(2, 1, 8, 4)           \
+  X(2, 2, 8, 4)           \
+  X(4, 2, 8, 3)           \
+  X(4, 4, 8, 2)
+bool ksplit_applicable(int dtype, int layout, int n, int c, int h, int w, int r, int s, int stride, int pad, int k,
+                       int c2);
+// the fp32 implicit GEMM's tile for m output pixels, k output channels and
+// a reduction of red: FM * 8 + FN of a wave-split tile, or 0 for the LDS
+// tile (lds_ok: whether that one can run the layer)
+int ksplit_pick_f32(long long m, int k, long long red, bool lds_ok);
+// the kernel's filter order: kp rows of row_bytes (a multiple of 16) as blocks
+// of 16 rows x 4 chunks of 16 bytes, each 1 KB in lane order
+size_t ksplit_packed_bytes(int kp, size_t row_bytes);
+void ksplit_pack(const void* w, int kp, size_t row_bytes, void* out);
+void conv_ksplit(int dtype, int fm, int fn, int nw, const ConvArgs& a, hipStream_t st);
 // Winograd F(m x m, 3x3), m = tile 2 or 4, as three sub-layers (a
 // childnet): sub 0 = input transform, 1 = the (m+2)^2 batched GEMMs with
 // GEMM tile `cfg` (one of winograd_gemm_num_configs), 2 = output transform;

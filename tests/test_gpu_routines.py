@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import numeric as O
+from paper_2110_06037_amd import Graph
 from tests.gpu_util import TOL, err, from_dev, oracle_layer, run_routine, single_layer_graph, to_dev
 from workloads import random_tensor, to_f64
 
@@ -463,4 +464,66 @@ def test_winograd_childnet_sub_routines(dtype):
             e = err(out, ref, dtype)
             print(f"{dtype} {r['name']} wgconv:p{q}: err {e:.2e}", flush=True)
             assert e <= TOL[dtype], (r["name"], q, e)
+    g.close()
+
+
+# The wave-split implicit GEMM (the 16-bit parameters from 106 on; in fp32 the
+# tile the one parameter takes by size): (N, C, H, W, K, R, stride, pad,
+# shortcut channels or None, residual).  Reductions shorter than a step, than
+# the waves, and no multiple of either; partial pixel and channel blocks; a
+# channel block past the last one; taps outside the image; sizes for which
+# fp32 takes each of its tiles (16x16, 32x16, 32x32 pixels x channels, LDS).
+WAVE_SPLIT_CASES = [
+    (1, 8, 1, 1, 8, 1, 1, 0, None, False),       # one pixel, one chunk
+    (3, 24, 5, 7, 40, 3, 2, 1, None, False),     # 27 chunks (54 in fp32), stride 2
+    (2, 40, 9, 9, 72, 5, 1, 2, None, True),      # 5x5, K = 4.5 blocks, residual
+    (1, 16, 6, 6, 20, 3, 1, 0, None, True),      # K % 8 != 0, no padding
+    (2, 20, 7, 5, 10, 3, 1, 1, None, False),     # C % 8 != 0: NC8HW8 only
+    (1, 512, 7, 7, 64, 1, 1, 0, 96, False),      # projected shortcut (at stride 2)
+    (2, 24, 9, 7, 40, 3, 1, 1, 8, False),        # ... with chunk counts that are no multiples of a step
+    (1, 256, 28, 28, 64, 3, 1, 1, None, False),  # fp32: 16 x 16
+    (3, 128, 23, 23, 72, 3, 1, 1, None, True),   # fp32: 32 x 16
+    (4, 128, 28, 28, 128, 3, 1, 1, None, False),  # fp32: 32 x 32
+    (4, 64, 56, 56, 64, 3, 1, 1, None, False),   # fp32: the LDS tile
+]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("ci", range(len(WAVE_SPLIT_CASES)))
+def test_wave_split_edges(dtype, ci):
+    n, c, h, w, k, r, st, pad, c2, res = WAVE_SPLIT_CASES[ci]
+    p, q = (h + 2 * pad - r) // st + 1, (w + 2 * pad - r) // st + 1
+    layer = {"type": "conv", "in": [0], "k": k, "r": r, "s": r, "stride": st, "pad": pad, "groups": 1, "act": "relu"}
+    second = (n, c2, 2 * p - 1, 2 * q - 1) if c2 else (n, k, p, q) if res else None
+    x = random_tensor((n, c, h, w), dtype, seed=500 + ci)
+    wt = random_tensor((k, c, r, r), dtype, seed=520 + ci, dist="normal", scale=np.sqrt(2 / (c * r * r)))
+    b = random_tensor((k,), "f32", seed=540 + ci, scale=0.1)
+    y = O.conv2d(to_f64(x, dtype), to_f64(wt, dtype), b.astype(np.float64), st, pad, 1, "none")
+    g = Graph(dtype, n, c, h, w, device=0)
+    xs = [to_dev(x, dtype)]
+    if second:
+        x2 = random_tensor(second, dtype, seed=560 + ci)
+        xs.append(to_dev(x2, dtype))
+        g.add_input(*second[1:])
+    if c2:
+        w2 = random_tensor((k, c2, 1, 1), dtype, seed=580 + ci, dist="normal", scale=np.sqrt(2 / c2))
+        g.add_projected_conv(0, 1, wt, b, w2, np.zeros(k, np.float32), st, pad, "relu", 2)
+        y = y + O.conv2d(to_f64(x2, dtype), to_f64(w2, dtype), np.zeros(k), 2, 0, 1, "none")
+    elif res:
+        g.add_conv(0, wt, b, st, pad, act="relu", residual=1)
+        y = y + to_f64(x2, dtype)
+    else:
+        g.add_spec(layer, wt, b)
+    ref = O.round_to(np.maximum(y, 0), dtype)
+    last = g.num_layers() - 1
+    mine = [rt for rt in g.routines(last) if rt["algo"] == 1 and (dtype == "f32" or rt["param"] >= 106)]
+    assert mine
+    if dtype != "f32":
+        assert {rt["layout"] for rt in mine} == ({1, 2} if c % 8 == 0 else {2})
+    for rt in mine:
+        g.set_path([0] * last + [rt["id"]])
+        out = from_dev(g.run_mimo(xs, output_layers=[last])[0], dtype)
+        # fp32: up to 2816 products in 8 partial sums, each sum's rounding at
+        # most 352 * 2^-24 of the sum of the products' magnitudes
+        assert err(out, ref, dtype) <= TOL[dtype], (rt["name"], err(out, ref, dtype))
     g.close()
