@@ -11,8 +11,8 @@ from oracle import numeric as O
 from oracle.select import blockwise, exhaustive, problem_from_costs
 from paper_2110_06037_amd import build_from_spec, native as N
 from tests.gpu_util import TOL, err, from_dev, to_dev
-from workloads import (CONV_SWEEP_SHAPES, conv_sweep, decode, fuse_projection, fuse_residual, generate, mobilenet_v2,
-                       resnet18, resnet50, tiny_chain, to_f64, vgg16, with_batch)
+from workloads import (CONV_SWEEP_SHAPES, conv_sweep, decode, fuse_projection, fuse_residual, generate, materialise,
+                       mobilenet_v2, resnet18, resnet50, tiny_chain, to_f64, vgg16, with_batch)
 
 pytestmark = pytest.mark.gpu
 
@@ -421,4 +421,42 @@ def test_plan_launch_list_matches_the_routines():
             assert n == 2, (i, rt["name"], n)
     out1, _ = run_out(g, spec, t)
     assert np.array_equal(out0, out1)
+    g.close()
+
+
+@pytest.mark.parametrize("hw,shared", [(20, True), (247, False)])
+def test_adapts_making_one_conversion_share_its_result(hw, shared):
+    # x enters the first convolution and, as the residual, the last one, both
+    # in NHWC: one converter serves both.  At 247 x 247 the converted copy,
+    # alive beside the two 256-channel maps, would take the plan past the 64 MiB
+    # of sn_run_noalloc, so that plan converts per edge and stays accepted.
+    import torch
+    from paper_2110_06037_amd import Graph
+    rng = np.random.default_rng(7)
+
+    def wts(k, c):
+        return materialise(rng.standard_normal((k, c, 1, 1)) * np.sqrt(2 / c), "bf16")
+    w = [wts(256, 64), wts(256, 256), wts(64, 256)]
+    b = [np.zeros(k, np.float32) for k in (256, 256, 64)]
+    g = Graph("bf16", 1, 64, hw, hw, layouts=["NHWC"], algos=["igemm"])
+    a = g.add_conv(0, w[0], b[0], act="relu")
+    a = g.add_conv(a, w[1], b[1], act="relu")
+    g.add_conv(a, w[2], b[2], act="relu", residual=0)
+    g.select("fixed", "NHWC", "igemm")
+    assert g.plan_launches() == ([1, 1, 2, 3, 3] if shared else [1, 1, 2, 3, 3, 3])
+    x = materialise(rng.standard_normal((1, 64, hw, hw)), "bf16")
+    xd = to_dev(x, "bf16")
+    out = g.run(xd)
+    f = [to_f64(v, "bf16").reshape(v.shape[:2]) for v in w]
+    px = to_f64(x, "bf16").reshape(64, -1)[:, ::97]
+    h = px
+    for m in f[:2]:
+        h = np.maximum(m @ h, 0)
+    ref = np.maximum(f[2] @ h + px, 0)
+    assert err(from_dev(out, "bf16").reshape(64, -1)[:, ::97], ref, "bf16") <= TOL["bf16"]
+    again, _ = g.run_timed(xd, reps=3)
+    out2 = torch.empty_like(out)
+    g.run_noalloc(xd, out2)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again) and torch.equal(out, out2)
     g.close()
