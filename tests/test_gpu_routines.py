@@ -241,6 +241,19 @@ def test_add_and_converters_bit_exact(dtype, c, hw):
                 assert np.array_equal(out, ref), ids
 
 
+def test_converter_past_the_register_transpose_limit():
+    # 34.5 MB of 16-bit values (past the 32 MiB up to which NCHW <-> NHWC
+    # transposes in registers): the LDS tile, with a partial channel tile
+    from paper_2110_06037_amd import Graph
+    n, c, h, w = 2, 136, 256, 248
+    x = random_tensor((n, c, h, w), "f16", seed=13, dist="int")
+    g = Graph("f16", n, c, h, w, device=0, layouts=["NHWC"])
+    g.add_maxpool(0, 1, 1, 0)
+    g.set_path([0, 0])
+    assert np.array_equal(from_dev(g.run(to_dev(x, "f16")), "f16"), to_f64(x, "f16"))
+    g.close()
+
+
 RESIDUAL_CASES = [
     # (N, C, H, W, R, act): K = C, stride 1, so the residual is an ADD of the input with itself
     (2, 64, 9, 11, 1, "relu"),      # pointwise, LDS-DMA tiles apply (C % 64 == 0)
