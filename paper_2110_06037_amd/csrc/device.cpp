@@ -61,10 +61,14 @@ struct Step {
   k::TDesc outd{};
   BufRef ws;
   size_t ws_bytes = 0;
+  int run = -1;  // layer whose routine the step launches (with `layer`'s addition when they differ)
 };
 
 struct Plan {
-  std::vector<Step> steps;
+  std::vector<Step> steps;  // every layer on its own (timed runs)
+  // what a run launches: the steps with some pairs of layers in one launch
+  // (same bits), each of its Steps in order
+  std::vector<Step> fused;
   void* arena = nullptr;
   size_t arena_bytes = 0;
   std::vector<int> first_step, last_step;  // per layer (steps of a layer are contiguous)
@@ -344,9 +348,11 @@ size_t routine_ws_bytes(const Graph& g, const Layer& L, const Routine& r) {
 
 // sub >= 0 launches only that sub-layer of a childnet routine, with
 // sub-routine sub_routine (unit profiling of the childnet's sub-routines)
+// add: an ADD layer computed in the convolution's epilogue, its other operand in[1]
 static void launch_layer(const Graph& g, int id, const Routine& r, const void* const* in,
                          const k::TDesc* ind, void* out, const k::TDesc& outd, void* ws,
-                         size_t ws_bytes, hipStream_t st, int sub = -1, int sub_routine = 0) {
+                         size_t ws_bytes, hipStream_t st, int sub = -1, int sub_routine = 0,
+                         const Layer* add = nullptr) {
   const Layer& L = g.layers[id];
   const DevLayer& dl = g.dev->L[id];
   const int dt = r.dtype;
@@ -368,7 +374,11 @@ static void launch_layer(const Graph& g, int id, const Routine& r, const void* c
       a.ws_bytes = ws_bytes;
       a.cnt = g.dev->fixup_cnt;
       a.wks = dl.wks[dt];
-      a.res = L.inputs.size() > 1 ? in[1] : nullptr;
+      a.res = L.inputs.size() > 1 || add ? in[1] : nullptr;
+      if (add) {
+        a.round_sum = true;
+        a.act = add->d.act;
+      }
       if (L.proj_stride > 0) {
         a.res = nullptr;
         if (r.algo == SN_ALGO_DIRECT) {
@@ -632,10 +642,30 @@ void dev_profile(Graph& g, int warmup, int reps, void* stream) {
 }
 
 // ------------------------------------------------------------------ plan
+// The convolution that can compute addition `a` in its epilogue, or -1: its
+// result goes to that addition alone, in the addition's schema, without an
+// activation, and its routine adds a residual with the same bits as the two
+// launches (the sum rounded to the type before the addition).  The later
+// of two such operands, so that the other one is ready.
+static int fusable_conv(const Graph& g, int a, const std::vector<int>& outs) {
+  const Layer& A = g.layers[a];
+  if (A.type != SN_LAYER_ADD || A.inputs[0] == A.inputs[1]) return -1;
+  const int c = std::max(A.inputs[0], A.inputs[1]);
+  const Layer& L = g.layers[c];
+  if (L.type != SN_LAYER_CONV2D || L.d.groups != 1 || L.d.act != SN_ACT_NONE || L.inputs.size() != 1) return -1;
+  if (std::find(outs.begin(), outs.end(), c) != outs.end()) return -1;
+  int readers = 0;
+  for (const Layer& o : g.layers) readers += (int)std::count(o.inputs.begin(), o.inputs.end(), c);
+  const Routine& r = L.routines[g.path[c]];
+  if (readers != 1 || r.schema() != A.routines[g.path[a]].schema() || r.algo != SN_ALGO_IGEMM) return -1;
+  return k::igemm_param_fuses_add(r.dtype, r.param, r.layout, L.d.k) ? c : -1;
+}
+
 // The steps of the selected path and their places in the arena (host
 // arithmetic only).  share: layers whose adapts make the same conversion of
 // the same tensor read one converted copy.
-static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share) {
+// fuse: an addition may run in its convolution's launch.
+static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share, bool fuse) {
   std::unique_ptr<Plan> P(new Plan);
   const int n = g.n_layers();
   const std::vector<int> outs = net_outputs(g);
@@ -728,6 +758,7 @@ static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share) {
         if (out_buf[j] >= 0) uses.push_back(out_buf[j]);
       }
     }
+    s.run = i;
     s.outd = tdesc(L.out, r.layout);
     const int out_k = (int)(std::find(outs.begin(), outs.end(), i) - outs.begin());
     const bool is_out = out_k < (int)outs.size();
@@ -763,6 +794,20 @@ static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share) {
       c.dst.kind = 2;
       c.dst.idx = out_k;
       push(c, {out_buf[i]});
+    }
+  }
+  // additions computed by a convolution's launch, in the addition's place:
+  // conv_of[k] is the convolution of addition k
+  std::vector<int> conv_of(n, -1), gone(n, 0);
+  if (fuse && !g.opt_keep) {
+    for (int a = 1; a < n; ++a) {
+      const int c = fusable_conv(g, a, outs);
+      if (c < 0) continue;
+      conv_of[a] = c;
+      gone[c] = 1;
+      // what the convolution reads stays until the addition's step (as does
+      // its workspace, and its own output, which only a timed run writes)
+      for (int b : step_bufs[P->last_step[c]]) bufs[b].last = std::max(bufs[b].last, P->last_step[a]);
     }
   }
   // first-fit offsets, largest buffers first; buffers whose step ranges
@@ -805,6 +850,20 @@ static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share) {
   P->layer_out = out_ref;
   for (BufRef& r : P->layer_out) resolve(r);
   P->arena_bytes = std::max<size_t>(total, 256);
+  for (const Step& s : P->steps) {
+    if (s.type == 1 && gone[s.layer]) continue;
+    if (s.type == 1 && conv_of[s.layer] >= 0) {
+      const int c = conv_of[s.layer];
+      Step f = P->steps[P->last_step[c]];
+      f.layer = s.layer;
+      f.n_in = 2;
+      f.in[1] = s.in[g.layers[s.layer].inputs[0] == c ? 1 : 0];
+      f.out = s.out;
+      P->fused.push_back(f);
+      continue;
+    }
+    P->fused.push_back(s);
+  }
   return P;
 }
 
@@ -812,11 +871,12 @@ void plan_compile(Graph& g) {
   HIPCHK(hipSetDevice(g.device));
   plan_destroy(g);
   const int n = g.n_layers();
-  std::unique_ptr<Plan> P = plan_layout(g, true);
-  // a shared copy lives to its last reader: a plan that fits the static
-  // region of sn_run_noalloc only without sharing converts per edge
+  std::unique_ptr<Plan> P = plan_layout(g, true, true);
+  // a shared copy lives to its last reader, and a convolution's input to the
+  // addition it computes: a plan that fits the static region of
+  // sn_run_noalloc only without them does without
   if (P->arena_bytes > noalloc_scratch_bytes()) {
-    std::unique_ptr<Plan> Q = plan_layout(g, false);
+    std::unique_ptr<Plan> Q = plan_layout(g, false, false);
     if (Q->arena_bytes <= noalloc_scratch_bytes()) P = std::move(Q);
   }
   HIPCHK(hipMalloc(&P->arena, P->arena_bytes));
@@ -835,16 +895,16 @@ static void enqueue_step(const Graph& g, const Plan& P, char* base, const Step& 
   if (s.type == 0) {
     k::convert_cast(s.sdt, ptr(s.src), s.sd, s.ddt, ptr(s.dst), s.dd, st);
   } else {
-    const Routine& r = g.layers[s.layer].routines[g.path[s.layer]];
+    const Routine& r = g.layers[s.run].routines[g.path[s.run]];
     const void* ins[2] = {ptr(s.in[0]), s.n_in > 1 ? ptr(s.in[1]) : nullptr};
-    launch_layer(g, s.layer, r, ins, s.ind, ptr(s.out), s.outd, s.ws_bytes ? ptr(s.ws) : nullptr,
-                 s.ws_bytes, st);
+    launch_layer(g, s.run, r, ins, s.ind, ptr(s.out), s.outd, s.ws_bytes ? ptr(s.ws) : nullptr,
+                 s.ws_bytes, st, -1, 0, s.run != s.layer ? &g.layers[s.layer] : nullptr);
   }
 }
 
 static void enqueue_steps(const Graph& g, const Plan& P, char* base, const void* const* d_in,
                           void* const* d_out, hipStream_t st) {
-  for (const Step& s : P.steps) enqueue_step(g, P, base, s, d_in, d_out, st);
+  for (const Step& s : P.fused) enqueue_step(g, P, base, s, d_in, d_out, st);
   HIPCHK(hipGetLastError());
 }
 
@@ -971,7 +1031,7 @@ std::vector<int> plan_launch_layers(const Graph& g) {
     ~Restore() { k::g_count_only = 0; }
   } restore;
   k::g_count_only = 1;
-  for (const Step& s : P.steps) {
+  for (const Step& s : P.fused) {
     const long long before = k::g_launches;
     enqueue_step(g, P, base, s, ins.data(), outs.data(), nullptr);
     for (long long q = before; q < k::g_launches; ++q) layer_of.push_back(s.layer);

@@ -51,8 +51,9 @@ struct KsArgs {
   int HW8;                  // NC8HW8: elements between channel blocks
   int Kp;                   // bias entries
   int act, tiles_m, tiles_n;
+  int round_sum;            // round the sum to the type before adding the residual
   float inv_pq, inv_q, inv_cb, inv_s;
-  long long x_elems, w_bytes;
+  long long x_elems, w_bytes, y_bytes;
   // projected shortcut
   const void* x2;
   const void* w2;
@@ -176,6 +177,52 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
   u32x4 fa[D][FM], fb[D][FN];
 #pragma unroll
   for (int d = 0; d < D; ++d) load(t0 + d, t1, fa[d], fb[d]);
+
+  // the thread's outputs: quads of four channels, e = tid + 64 NW u;
+  // consecutive threads on consecutive addresses (NHWC: a pixel's channels;
+  // NC8HW8: the pixels of a channel block).  The residual is loaded here, under
+  // the reduction: after it, a load's latency would be most of the epilogue.
+  constexpr int NQ = (BM * BN / 4 + 64 * NW - 1) / (64 * NW);
+  constexpr bool ALL = BM * BN / 4 % (64 * NW) == 0;  // every thread has NQ quads
+  const bool vec = L == NC8 || a.Ks % 4 == 0;
+  const T* __restrict__ res = reinterpret_cast<const T*>(a.res);
+  int qm[NQ], qn[NQ];
+  unsigned qo[NQ];  // element offset, or kOOB
+  f32x4 rq[NQ];     // the residual's 8 or 16 bytes
+#pragma unroll
+  for (int u = 0; u < NQ; ++u) {
+    const int e = tid + 64 * NW * u;
+    if constexpr (L == NC8) {
+      qm[u] = (e >> 1) % BM;
+      qn[u] = (e >> 1) / BM * 8 + (e & 1) * 4;
+    } else {
+      qm[u] = e / (BN / 4);
+      qn[u] = e % (BN / 4) * 4;
+    }
+    const int m = m0 + qm[u], n = n0 + qn[u];
+    unsigned o;
+    if constexpr (L == NC8) {
+      const int img = sdiv(m, a.inv_pq), pq = m - img * a.PQ;
+      o = (unsigned)(((img * (a.Ks >> 3) + (n >> 3)) * a.PQ + pq) * 8 + (n & 7));
+    } else {
+      o = (unsigned)(m * a.Ks + n);
+    }
+    qo[u] = (ALL || e < BM * BN / 4) && m < a.M && n < a.Ng ? o : kOOB;
+    rq[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  if (res && vec) {
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(res, a.y_bytes);
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+      const int off = qo[u] == kOOB ? (int)kOOB : (int)(qo[u] * ES);
+      if constexpr (ES == 4) {
+        rq[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, off, 0, 0));
+      } else {
+        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rr, off, 0, 0));
+        __builtin_memcpy(&rq[u], &v, 8);
+      }
+    }
+  }
   for (int t = t0; t < t1; t += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -196,51 +243,35 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
       *reinterpret_cast<f32x4*>(mine + (i * 16 + row) * RP + j * 16 + grp * 4) = acc[i][j];
   __syncthreads();
 
-  const ActClamp ac = act_clamp(a.act);
   T* __restrict__ y = reinterpret_cast<T*>(a.y);
-  const T* __restrict__ res = reinterpret_cast<const T*>(a.res);
-  const bool vec = L == NC8 || a.Ks % 4 == 0;
-  // four channels per thread; consecutive threads on consecutive addresses
-  // (NHWC: a pixel's channels; NC8HW8: the pixels of a channel block)
-  for (int e = tid; e < BM * BN / 4; e += 64 * NW) {
-    int ml, nl;
-    if constexpr (L == NC8) {
-      ml = (e >> 1) % BM;
-      nl = (e >> 1) / BM * 8 + (e & 1) * 4;
-    } else {
-      ml = e / (BN / 4);
-      nl = e % (BN / 4) * 4;
-    }
-    const int m = m0 + ml, n = n0 + nl;
-    if (m >= a.M || n >= a.Ng) continue;
-    f32x4 s = *reinterpret_cast<const f32x4*>(red + ml * RP + nl);
 #pragma unroll
-    for (int v = 1; v < NW; ++v) s += *reinterpret_cast<const f32x4*>(red + (v * BM + ml) * RP + nl);
-    long long o;
-    if constexpr (L == NC8) {
-      const int img = sdiv(m, a.inv_pq), pq = m - img * a.PQ;
-      o = ((long long)(img * (a.Ks >> 3) + (n >> 3)) * a.PQ + pq) * 8 + (n & 7);
-    } else {
-      o = (long long)m * a.Ks + n;
-    }
+  for (int u = 0; u < NQ; ++u) {
+    if (qo[u] == kOOB) continue;
+    const int n = n0 + qn[u];
+    f32x4 s = *reinterpret_cast<const f32x4*>(red + qm[u] * RP + qn[u]);
+#pragma unroll
+    for (int v = 1; v < NW; ++v) s += *reinterpret_cast<const f32x4*>(red + (v * BM + qm[u]) * RP + qn[u]);
+    T* const yp = y + qo[u];
     T out[4], rt[4];
+    __builtin_memcpy(rt, &rq[u], 4 * ES);
     if (vec) {
-      if (res) __builtin_memcpy(rt, __builtin_assume_aligned(res + o, 4 * ES), 4 * ES);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        // bias holds Kp >= n + 4 - (Kp - K) entries; rows past it add zero
-        float f = s[v] + (n + v < a.Kp ? a.bias[n + v] : 0.f);
+        // the padded channels of NC8HW8 have a bias of zero (Kp entries)
+        float f = s[v] + a.bias[n + v];
+        if (a.round_sum) f = to_f(from_f<T>(f));
         if (res) f += to_f(rt[v]);
-        out[v] = from_f<T>(__builtin_amdgcn_fmed3f(f, ac.lo, ac.hi));
+        out[v] = from_f<T>(act_f(f, a.act));
       }
-      __builtin_memcpy(__builtin_assume_aligned(y + o, 4 * ES), out, 4 * ES);
+      __builtin_memcpy(__builtin_assume_aligned(yp, 4 * ES), out, 4 * ES);
     } else {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         if (n + v >= a.Ng) break;
         float f = s[v] + a.bias[n + v];
-        if (res) f += to_f(res[o + v]);
-        y[o + v] = from_f<T>(__builtin_amdgcn_fmed3f(f, ac.lo, ac.hi));
+        if (a.round_sum) f = to_f(from_f<T>(f));
+        if (res) f += to_f(res[qo[u] + v]);
+        yp[v] = from_f<T>(act_f(f, a.act));
       }
     }
   }
@@ -370,11 +401,13 @@ void conv_ksplit(int dtype, int fm, int fn, int nw, const ConvArgs& c, hipStream
   a.HW8 = a.H * a.W * 8;
   a.Kp = (c.yd.c + 7) / 8 * 8;
   a.act = c.act;
+  a.round_sum = c.round_sum;
   a.inv_pq = 1.f / (float)a.PQ;
   a.inv_q = 1.f / (float)a.Q;
   a.inv_cb = 1.f / (float)a.CBc;
   a.inv_s = 1.f / (float)a.S;
   a.x_elems = (long long)c.xd.n * c.xd.cs * c.xd.h * c.xd.w;
+  a.y_bytes = (long long)c.yd.n * c.yd.cs * c.yd.h * c.yd.w * es;
   a.w_bytes = (long long)ksplit_packed_bytes(a.Kp, (size_t)c.r * c.s * c8 * es);
   if (c.x2) {
     check(c.w2ks && c.x2d.layout == c.xd.layout && c.x2d.n == c.xd.n && (c.x2d.h - 1) / c.stride2 + 1 == c.yd.h &&

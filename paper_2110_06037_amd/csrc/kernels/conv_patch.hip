@@ -48,6 +48,8 @@ struct PatchArgs {
   const void* x;
   const void* w;  // [Kp][3][3][C8]
   const float* bias;
+  const void* res;     // an addition's other operand in the output's layout (the sum is rounded
+                       // before it and the activation comes after it), or null
   void* y;
   int N, C, H, W, Cs;  // input (pad 1)
   int K, P, Q, Ks, Ng;
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
   // rows of the GEMM (whole rows of one image, or whole images).
   constexpr int OP = BN * 2 + 16;  // staging row bytes
   static_assert(FMT * 16 * OP <= SM, "output staging fits the tile's LDS");
-  const ActClamp ac = act_clamp(a.act);
+  const ActClamp ac = act_clamp(a.res ? ACT_NONE : a.act);
   __syncthreads();  // every wave is done with the stages (and group 0 with group 1's sums)
   if (grp == 0) {
 #pragma unroll
@@ -337,7 +339,8 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
   const __amdgpu_buffer_rsrc_t ry = make_rsrc(y, a.y_elems * 2);
   constexpr int CPX = BN / 8;  // 16-byte chunks per pixel
   const bool vec8 = L == NC8 || a.Ks % 8 == 0;
-  for (int q = tid; q < valid * CPX; q += NWV * 64) {
+  // chunk q of the tile: its staged outputs (LDS byte) and element offset
+  auto chunk = [&](int q, int& lds, unsigned& e, int& n) {
     int ml, c8;
     if constexpr (L == NC8) {
       c8 = q / valid;
@@ -346,17 +349,53 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
       ml = q / CPX;
       c8 = q - ml * CPX;
     }
-    const int n = n0 + c8 * 8;
-    if (n >= a.Ng) continue;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(smem + ml * OP + c8 * 16);
+    n = n0 + c8 * 8;
+    lds = ml * OP + c8 * 16;
     const int m = mbase + ml;
-    unsigned e;
     if constexpr (L == NC8) {
       const int img = sdiv(m, a.inv_pq), pq = m - img * PQ;
       e = (unsigned)(((img * (a.Ks >> 3) + (n >> 3)) * PQ + pq) * 8);
     } else {
       e = (unsigned)(m * a.Ks + n);
     }
+  };
+  if (a.res) {
+    // the addition: all of a thread's residual chunks are loaded before the
+    // first is used (out-of-range offsets past the tile load and store
+    // nothing); the host admits whole 16-byte chunks only
+    constexpr int NC = (FMT * 16 * CPX + NWV * 64 - 1) / (NWV * 64);
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, a.y_elems * 2);
+    u32x4 rv[NC];
+    unsigned off[NC];
+    int ls[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int q = tid + c * NWV * 64;
+      int n;
+      unsigned e;
+      chunk(q < valid * CPX ? q : 0, ls[c], e, n);
+      off[c] = q < valid * CPX && n < a.Ng ? e * 2u : kOOB;
+      rv[c] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[c], 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      T o[8], r[8];
+      __builtin_memcpy(o, smem + ls[c], 16);
+      __builtin_memcpy(r, &rv[c], 16);
+#pragma unroll
+      for (int v = 0; v < 8; ++v) o[v] = from_f<T>(act_f(to_f(o[v]) + to_f(r[v]), a.act));
+      u32x4 pk;
+      __builtin_memcpy(&pk, o, 16);
+      __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[c], 0, 0);
+    }
+    return;
+  }
+  for (int q = tid; q < valid * CPX; q += NWV * 64) {
+    int lds, n;
+    unsigned e;
+    chunk(q, lds, e, n);
+    if (n >= a.Ng) continue;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(smem + lds);
     if (vec8 && n + 8 <= a.Ng) {
       __builtin_amdgcn_raw_buffer_store_b128(v, ry, (int)(e * 2u), 0, 0);
     } else {
@@ -411,6 +450,7 @@ static PatchArgs make_patch(const ConvArgs& c) {
   a.x = c.x;
   a.w = c.w;
   a.bias = c.bias;
+  a.res = c.res;
   a.y = c.y;
   a.N = c.xd.n;
   a.C = c.xd.c;
@@ -504,6 +544,8 @@ void conv_patch(int dtype, const PatchCfg& cfg, const ConvArgs& c, hipStream_t s
         "patch kernel: 3x3 pad 1 at the tile's stride, one layout");
   check(c.xd.layout == NC8 || (c.xd.layout == NHWC && c.xd.c % 8 == 0), "patch kernel: channel-vector layout");
   check((long long)c.yd.n * c.yd.cs * c.yd.h * c.yd.w * 2 < (long long)kOOB, "tensor too large");
+  check(!c.res || (c.round_sum && (c.yd.layout == NC8 || c.yd.cs % 8 == 0)),
+        "patch kernel: an addition after the rounded sum, whole 16-byte chunks");
   const PatchArgs a = make_patch(c);
   if (dtype == 1) {
     if (c.xd.layout == NC8) patch_layout<f16, NC8>(cfg, a, st);

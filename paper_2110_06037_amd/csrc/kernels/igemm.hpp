@@ -1389,7 +1389,9 @@ static void igemm_dispatch(int dtype, int param, const ConvArgs& c, hipStream_t 
       }
     }
   }
-  check(!c.res || cfg.dma == 0 || ((cfg.dma == 1 || cfg.dma == 4) && (c.yd.layout == NC8 || c.yd.cs % 8 == 0)),
+  check(!c.round_sum || (c.res && igemm_param_fuses_add(dtype, param, c.yd.layout, c.yd.c)),
+        "this tile configuration does not compute a following addition");
+  check(!c.res || cfg.dma == 0 || (cfg.dma == 2 && c.round_sum) || ((cfg.dma == 1 || cfg.dma == 4) && (c.yd.layout == NC8 || c.yd.cs % 8 == 0)),
         "this tile configuration takes no residual");
   check(!c.x2 || cfg.dma == 4 ||
             (cfg.dma == 1 && cfg.split != 1 && !c.res && c.x2d.layout == c.xd.layout &&

@@ -63,6 +63,8 @@ struct ConvArgs {
   size_t ws_bytes;
   const void* res = nullptr;  // residual of the output's shape and layout, added before the
                               // activation (direct and implicit-GEMM routines), or null
+  bool round_sum = false;     // round the sum to the type before adding the residual (the bits of
+                              // a convolution and an addition; igemm_param_fuses_add)
   unsigned* cnt = nullptr;    // kFixupMaxTiles tile counters for reductions split across
                               // workgroups: zero before a launch, zero again after it
   // projected shortcut (implicit GEMM on the LDS-DMA tiles): x2 read by a
@@ -89,6 +91,9 @@ int igemm_first_appended_param(int dtype);
 // whether the tile configuration adds a residual in its epilogue (for an
 // output of k channels in the layout)
 bool igemm_param_takes_residual(int dtype, int param, int layout, int k);
+// whether the tile configuration also adds it after rounding its sum
+// (ConvArgs::round_sum: a convolution and the ADD layer after it in one launch)
+bool igemm_param_fuses_add(int dtype, int param, int layout, int k);
 bool igemm_param_valid(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
                        int stride, int pad, int k);
 // whether the tile configuration takes a projected shortcut of c2 channels

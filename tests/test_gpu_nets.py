@@ -460,3 +460,56 @@ def test_adapts_making_one_conversion_share_its_result(hw, shared):
     torch.cuda.synchronize()
     assert torch.equal(out, again) and torch.equal(out, out2)
     g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+# (C, K, H, W, R, act, addition's operand order): ragged pixel and channel
+# tiles; K % 8 != 0 (element stores); every patch tile applies at 64 channels
+@pytest.mark.parametrize("case", [(64, 64, 14, 14, 3, "relu", 0), (64, 72, 28, 28, 3, "none", 1),
+                                  (32, 20, 9, 7, 3, "relu6", 0), (24, 40, 5, 6, 1, "relu", 1),
+                                  (64, 64, 56, 56, 3, "relu", 0)])
+def test_addition_in_its_convolutions_launch(dtype, case):
+    # a convolution read by one addition alone, in its schema, without an
+    # activation: one launch, with the bits of the two (a timed run makes both)
+    import torch
+    from paper_2110_06037_amd import Graph
+    c, k, h, w, r, act, order = case
+    n = 2
+    rng = np.random.default_rng(11)
+    wt = materialise(rng.standard_normal((k, c, r, r)) * np.sqrt(2 / (c * r * r)), dtype)
+    b = rng.uniform(-0.1, 0.1, k).astype(np.float32)
+    x = materialise(rng.uniform(-1, 1, (n, c, h, w)), dtype)
+    x2 = materialise(rng.uniform(-1, 1, (n, k, h, w)), dtype)
+    x2.reshape(-1)[3] = materialise(np.array([np.inf]), dtype)[0]
+    ref = O.round_to(O.conv2d(to_f64(x, dtype), to_f64(wt, dtype), b.astype(np.float64), 1, r // 2), dtype)
+    ref = O.round_to(O.add(ref, to_f64(x2, dtype), act), dtype).reshape(-1)
+    fin = np.isfinite(ref)
+    g = Graph(dtype, n, c, h, w, device=0, algos=["igemm"])
+    i2 = g.add_input(k, h, w)
+    cv = g.add_conv(0, wt, b, pad=r // 2)
+    a = g.add_add(*((cv, i2) if order else (i2, cv)), act)
+    adds = {rt["layout"]: rt["id"] for rt in g.routines(a)}
+    xs = [to_dev(x, dtype), to_dev(x2, dtype)]
+    fused = set()
+    for rt in g.routines(cv):
+        if rt["algo"] != N.IGEMM:
+            continue
+        g.set_path([0, 0, rt["id"], adds[rt["layout"]]])
+        lay = g.plan_launches()
+        if cv in lay and lay.count(cv) > (1 if rt["layout"] else 0):
+            continue                                             # two launches
+        fused.add(rt["param"])
+        out = g.run_mimo(xs, output_layers=[a])[0]
+        got = from_dev(out, dtype).reshape(-1)
+        assert err(got[fin], ref[fin], dtype) <= TOL[dtype], rt["name"]
+        assert not np.isfinite(got[~fin]).any() if act != "relu6" else (got[~fin] == 6).all(), rt["name"]
+        g.set_option(N.OPT_KEEP, 1)                              # both layers' outputs kept: two launches
+        assert g.plan_launches().count(cv) > lay.count(cv)
+        two = g.run_mimo(xs, output_layers=[a])[0]
+        torch.cuda.synchronize()
+        assert torch.equal(out, two), rt["name"]
+        g.set_option(N.OPT_KEEP, 0)
+    assert fused if dtype == "f32" else {p for p in fused if p >= 106}
+    if dtype != "f32" and r == 3 and k % 8 == 0 and c == 64:
+        assert {p for p in fused if p < 106}                     # patch tiles too
+    g.close()
