@@ -73,6 +73,8 @@ struct Plan {
   size_t arena_bytes = 0;
   std::vector<int> first_step, last_step;  // per layer (steps of a layer are contiguous)
   std::vector<BufRef> layer_out;           // per layer: where its routine stores its output
+  std::unique_ptr<Plan> tight;             // the layout for the static region of sn_run_noalloc,
+                                           // when this one is larger than that (no arena of its own)
   std::vector<hipEvent_t> ev;              // timed runs: 2 per layer
   hipStream_t gstream = nullptr;           // stream the captured graph replays on
   hipGraphExec_t gexec = nullptr;
@@ -664,8 +666,9 @@ static int fusable_conv(const Graph& g, int a, const std::vector<int>& outs) {
 // The steps of the selected path and their places in the arena (host
 // arithmetic only).  share: layers whose adapts make the same conversion of
 // the same tensor read one converted copy.
-// fuse: an addition may run in its convolution's launch.
-static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share, bool fuse) {
+// fuse: an addition may run in its convolution's launch.  hold: steps after a
+// buffer's last reader during which no other buffer takes its bytes.
+static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share, bool fuse, int hold) {
   std::unique_ptr<Plan> P(new Plan);
   const int n = g.n_layers();
   const std::vector<int> outs = net_outputs(g);
@@ -819,10 +822,11 @@ static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share, bool fuse) 
   });
   std::vector<int> placed;
   size_t total = 0;
+  auto held = [&](const Buf& b) { return (int64_t)b.last + hold; };
   for (int b : order) {
     std::vector<std::pair<size_t, size_t>> busy;
     for (int o : placed)
-      if (!(bufs[o].last < bufs[b].def || bufs[b].last < bufs[o].def))
+      if (!(held(bufs[o]) < bufs[b].def || held(bufs[b]) < bufs[o].def))
         busy.push_back({bufs[o].off, bufs[o].off + bufs[o].bytes});
     std::sort(busy.begin(), busy.end());
     size_t off = 0;
@@ -871,14 +875,37 @@ void plan_compile(Graph& g) {
   HIPCHK(hipSetDevice(g.device));
   plan_destroy(g);
   const int n = g.n_layers();
-  std::unique_ptr<Plan> P = plan_layout(g, true, true);
-  // a shared copy lives to its last reader, and a convolution's input to the
-  // addition it computes: a plan that fits the static region of
-  // sn_run_noalloc only without them does without
-  if (P->arena_bytes > noalloc_scratch_bytes()) {
-    std::unique_ptr<Plan> Q = plan_layout(g, false, false);
-    if (Q->arena_bytes <= noalloc_scratch_bytes()) P = std::move(Q);
+  std::unique_ptr<Plan> P = plan_layout(g, true, true, 0);
+  // sn_run_noalloc runs in a static region: where the plan below is too large
+  // for it, the tightest layout that fits is kept beside it (a shared copy
+  // lives to its last reader, and a convolution's input to the addition it
+  // computes, so a layout without them can be smaller)
+  const size_t region = noalloc_scratch_bytes();
+  std::unique_ptr<Plan> tight;
+  if (P->arena_bytes <= region) {
+    tight = plan_layout(g, true, true, 0);
+  } else {
+    tight = plan_layout(g, false, false, 0);
+    if (tight->arena_bytes > region) tight.reset();
   }
+  // Bytes that a kernel has just read or written are slow to overwrite (their
+  // lines sit in other XCDs' caches), so a dead buffer's bytes rest for as
+  // many steps as the arena stays within 150 MiB, which the 256 MB Infinity
+  // Cache holds beside weights and caller's tensors.  us per run by steps of rest:
+  // ResNet-50 batch 32 641 (0: 110 MiB), 627 (1), 626 (2: 147 MiB), 681 (4: 208),
+  // 722 (no reuse: 608); batch 8 426 (0), 411 (1), 397 (4 to no reuse: 157 MiB);
+  // 512 x 28 x 28 bottlenecks at batch 8 86.5 (0), 84.4 (1), 81.4 (4), 80.2 (no reuse).  A
+  // plan past 150 MiB without rest streams anyway and is packed as tightly as before:
+  // ResNet-50 batch 64 1089 (0: 220 MiB), 1109 (1).
+  const size_t spread = size_t(150) << 20;
+  static const int holds[] = {INT32_MAX, 8, 4, 2, 1};
+  for (int hold : holds) {
+    std::unique_ptr<Plan> Q = plan_layout(g, true, true, hold);
+    if (Q->arena_bytes > spread) continue;
+    P = std::move(Q);
+    break;
+  }
+  if (P->arena_bytes > region) P->tight = std::move(tight);
   HIPCHK(hipMalloc(&P->arena, P->arena_bytes));
   P->ev.resize(2 * n, nullptr);
   for (auto& e : P->ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
@@ -1006,7 +1033,7 @@ void plan_run(Graph& g, const void* const* d_in, void* const* d_out, void* strea
 void plan_run_in(const Graph& g, void* base, size_t cap, const void* const* d_in, void* const* d_out,
                  void* stream) {
   if (!g.plan) fail(SN_E_STATE, "no execution plan");
-  const Plan& P = *g.plan;
+  const Plan& P = g.plan->tight ? *g.plan->tight : *g.plan;
   if (P.arena_bytes > cap)
     fail(SN_E_UNSUPPORTED, "the plan needs " + std::to_string(P.arena_bytes) +
                                " bytes of intermediate memory, more than the " + std::to_string(cap) +
@@ -1015,7 +1042,10 @@ void plan_run_in(const Graph& g, void* base, size_t cap, const void* const* d_in
   enqueue_steps(g, P, static_cast<char*>(base), d_in, d_out, static_cast<hipStream_t>(stream));
 }
 
-size_t plan_arena_bytes(const Graph& g) { return g.plan ? g.plan->arena_bytes : 0; }
+// what sn_run_noalloc needs
+size_t plan_arena_bytes(const Graph& g) {
+  return !g.plan ? 0 : g.plan->tight ? g.plan->tight->arena_bytes : g.plan->arena_bytes;
+}
 
 // The layer each kernel launch of one sn_run belongs to, in launch order
 // (converters feeding a layer count as the layer's).  The plan's steps are
