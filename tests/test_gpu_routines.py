@@ -540,3 +540,22 @@ def test_wave_split_edges(dtype, ci):
         # most 352 * 2^-24 of the sum of the products' magnitudes
         assert err(out, ref, dtype) <= TOL[dtype], (rt["name"], err(out, ref, dtype))
     g.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (2, 9, 3, 5), (1, 17, 8, 8), (3, 67, 15, 17), (1, 66, 16, 16),
+                                   (8, 2048, 4, 4), (9, 1821, 7, 7), (5, 3277, 2, 4)])
+def test_gap_planes_edges(dtype, shape):
+    """Last workgroups of few planes, runs that are no multiple of 16 bytes,
+    pitches that meet in one bank, both lane counts (from 16384 planes: 4 per
+    plane), the largest plane; on a tensor that is not 16-byte aligned too."""
+    import torch
+    x = random_tensor(shape, dtype, seed=17)
+    ref = oracle_layer({"type": "gap", "in": [0]}, x, None, None, dtype)
+    g = single_layer_graph(dtype, shape, {"type": "gap", "in": [0]}, layouts=["NCHW"])
+    xd = to_dev(x, dtype)
+    off = torch.empty(xd.numel() + 1, dtype=xd.dtype, device="cuda")[1:].view(shape).copy_(xd)
+    for t in (xd, off):
+        out = from_dev(run_routine(g, 0, t), dtype).reshape(ref.shape)
+        assert err(out, ref, dtype) <= TOL[dtype] * 0.1
+    g.close()
