@@ -1,7 +1,7 @@
 // Convolution as an implicit GEMM whose reduction is split over the waves of
 // a workgroup, for launches that are too small to be bound by anything but
 // latency (an implicit-GEMM routine; NHWC with C % 8 == 0 or NC8HW8, all
-// element types).
+// element types; NCHW in fp32).
 //
 // The tiled implicit GEMMs move each reduction step of a tile through LDS:
 // fill, wait, barrier, read, compute.  At a small batch their few workgroups
@@ -28,7 +28,11 @@
 // rows of [Kp][R][S][C8] touch 16).  An fp32 step is four 4-wide MFMAs; element e of the four lane
 // groups' chunks forms the reduction of the e-th.  The chunk's tap and
 // channel block come from an exact fp32 division, so channel counts need not
-// be multiples of the step.  A projected shortcut (PJ) appends the steps of its own
+// be multiples of the step.  In NCHW a chunk's four channels are four 4-byte loads
+// from their planes (channels past C read as zero), which coalesce over the
+// lanes' pixels, and the outputs go out element by element along the pixels;
+// small nets in fp32 stay in NCHW, where two converters would cost more than a
+// layer.  A projected shortcut (PJ) appends the steps of its own
 // tensor and filter.
 #include "gemm_common.hpp"
 #include "kcommon.hpp"
@@ -79,7 +83,7 @@ __device__ __forceinline__ f32x4 ks_mma(u32x4 w, u32x4 x, f32x4 c) {
 // K1: a 1x1 convolution without padding (no taps to decode)
 template <typename T, int L, int FM, int FN, int NW, int D, bool K1, bool PJ>
 __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
-  static_assert(L != NCHW, "channel-vector layouts only");
+  static_assert(L != NCHW || (sizeof(T) == 4 && !PJ), "NCHW: fp32 without a projected shortcut");
   constexpr int ES = sizeof(T), CE = 16 / ES;  // bytes and elements per chunk
   constexpr int BM = 16 * FM, BN = 16 * FN;
   constexpr int RP = BN + 4;                   // staging row pitch (floats)
@@ -109,6 +113,7 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
     h0[i] = mok[i] ? p * a.stride - a.pad : -(1 << 20);
     w0[i] = q * a.stride - a.pad;
     if constexpr (L == NC8) xbase[i] = (img * (a.Cs >> 3) * a.H + p * a.stride - a.pad) * (a.W * 8) + w0[i] * 8;
+    else if constexpr (L == NCHW) xbase[i] = (img * a.Cs * a.H + p * a.stride - a.pad) * a.W + w0[i];
     else xbase[i] = ((img * a.H + p * a.stride - a.pad) * a.W + w0[i]) * a.Cs;
     if constexpr (PJ) {
       const int h2 = p * a.stride2, w2 = q * a.stride2;
@@ -124,9 +129,11 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
     if constexpr (PJ) w2ofs[j] = (unsigned)(n0 / 16 + j) * (unsigned)a.steps2 * 1024u + lane * 16u;
   }
 
+  const int plane = a.H * a.W;  // NCHW: elements between channels
   // offset of chunk cc of a pixel's channels
   auto chunk_off = [&](int cc, int hw8) {
-    if constexpr (L == NC8) return CE == 8 ? cc * hw8 : (cc >> 1) * hw8 + (cc & 1) * 4;
+    if constexpr (L == NCHW) return cc * CE * plane;
+    else if constexpr (L == NC8) return CE == 8 ? cc * hw8 : (cc >> 1) * hw8 + (cc & 1) * 4;
     else return cc * CE;
   };
   auto load = [&](int t, int t1, u32x4 (&fa)[FM], u32x4 (&fb)[FN]) {
@@ -140,7 +147,7 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
         r = sdiv(tap, a.inv_s);
         s = tap - r * a.S;
       }
-      const int d = (K1 ? 0 : L == NC8 ? (r * a.W + s) * 8 : (r * a.W + s) * a.Cs) + chunk_off(cc, a.HW8);
+      const int d = (K1 ? 0 : (r * a.W + s) * (L == NC8 ? 8 : L == NCHW ? 1 : a.Cs)) + chunk_off(cc, a.HW8);
 #pragma unroll
       for (int j = 0; j < FN; ++j)
         fb[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, t < t1 ? (int)(wofs[j] + t * 1024u) : (int)kOOB, 0, 0);
@@ -148,7 +155,14 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
       for (int i = 0; i < FM; ++i) {
         const bool ok = K1 ? in && mok[i]
                            : in && (unsigned)(h0[i] + r) < (unsigned)a.H && (unsigned)(w0[i] + s) < (unsigned)a.W;
-        fa[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? (int)((unsigned)(xbase[i] + d) * ES) : (int)kOOB, 0, 0);
+        if constexpr (L == NCHW) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            fa[i][e] = __builtin_amdgcn_raw_buffer_load_b32(
+                rx, ok && cc * 4 + e < a.Cs ? (int)((unsigned)(xbase[i] + d + e * plane) * ES) : (int)kOOB, 0, 0);
+        } else {
+          fa[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? (int)((unsigned)(xbase[i] + d) * ES) : (int)kOOB, 0, 0);
+        }
       }
     } else {
       const int qk = (t - a.steps) * 4 + grp;
@@ -178,17 +192,18 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
 #pragma unroll
   for (int d = 0; d < D; ++d) load(t0 + d, t1, fa[d], fb[d]);
 
-  // the thread's outputs: quads of four channels, e = tid + 64 NW u;
+  // the thread's outputs (NCHW: see the end): quads of four channels, e = tid + 64 NW u;
   // consecutive threads on consecutive addresses (NHWC: a pixel's channels;
   // NC8HW8: the pixels of a channel block).  The residual is loaded here, under
   // the reduction: after it, a load's latency would be most of the epilogue.
-  constexpr int NQ = (BM * BN / 4 + 64 * NW - 1) / (64 * NW);
+  constexpr int NQ = L == NCHW ? 0 : (BM * BN / 4 + 64 * NW - 1) / (64 * NW);
   constexpr bool ALL = BM * BN / 4 % (64 * NW) == 0;  // every thread has NQ quads
   const bool vec = L == NC8 || a.Ks % 4 == 0;
   const T* __restrict__ res = reinterpret_cast<const T*>(a.res);
-  int qm[NQ], qn[NQ];
-  unsigned qo[NQ];  // element offset, or kOOB
-  f32x4 rq[NQ];     // the residual's 8 or 16 bytes
+  constexpr int NQA = NQ ? NQ : 1;
+  int qm[NQA], qn[NQA];
+  unsigned qo[NQA];  // element offset, or kOOB
+  f32x4 rq[NQA];     // the residual's 8 or 16 bytes
 #pragma unroll
   for (int u = 0; u < NQ; ++u) {
     const int e = tid + 64 * NW * u;
@@ -210,7 +225,7 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
     qo[u] = (ALL || e < BM * BN / 4) && m < a.M && n < a.Ng ? o : kOOB;
     rq[u] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (res && vec) {
+  if (NQ && res && vec) {
     const __amdgpu_buffer_rsrc_t rr = make_rsrc(res, a.y_bytes);
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
@@ -244,6 +259,20 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(KsArgs a) {
   __syncthreads();
 
   T* __restrict__ y = reinterpret_cast<T*>(a.y);
+  if constexpr (L == NCHW) {  // consecutive threads on consecutive pixels of a channel
+    for (int e = tid; e < BM * BN; e += 64 * NW) {
+      const int mm = e % BM, m = m0 + mm, nn = e / BM, n = n0 + nn;
+      if (m >= a.M || n >= a.Ng) continue;
+      float s = red[mm * RP + nn];
+#pragma unroll
+      for (int v = 1; v < NW; ++v) s += red[(v * BM + mm) * RP + nn];
+      const int img = sdiv(m, a.inv_pq), pq = m - img * a.PQ;
+      const unsigned o = (unsigned)((img * a.Ks + n) * a.PQ + pq);
+      s += a.bias[n];
+      if (res) s += to_f(res[o]);
+      y[o] = from_f<T>(act_f(s, a.act));
+    }
+  }
 #pragma unroll
   for (int u = 0; u < NQ; ++u) {
     if (qo[u] == kOOB) continue;
@@ -305,7 +334,12 @@ void ksplit_pack(const void* w, int kp, size_t row_bytes, void* out) {
 // nothing where the model cannot tell them apart.  The picks took these launches 1.6 times
 // faster than the LDS tile alone in the geometric mean: 128 channels 3x3 at
 // 3 x 23 x 23, 29.4 -> 11.1 us; 512 channels at 7 x 7, 103 -> 12.3 us.
-int ksplit_pick_f32(long long m, int k, long long red, bool lds_ok) {
+// In NCHW (red counts the filter's padded channels) the LDS tile gathers
+// element by element, 1.26 us per step (18 launches of 27 to 4608 products), and a
+// wave-split step has four times the loads, 1.65 of its NHWC time.  LDS tile ->
+// pick: 16 channels 3x3/2 at 32 x 32, 10.3 -> 5.1 us; 64 at 2 x 28 x 28, 28.0 -> 9.2; 512
+// at 7 x 7, 188 -> 14.9; 256 at 8 x 14 x 14, 98 -> 39.
+int ksplit_pick_f32(int layout, long long m, int k, long long red, bool lds_ok) {
   struct Fit {
     int fm, fn;
     double step, tile;
@@ -315,12 +349,13 @@ int ksplit_pick_f32(long long m, int k, long long red, bool lds_ok) {
   int pick = 0;
   if (lds_ok) {
     const double r = std::max(1.0, (double)(((m + 63) / 64) * ((k + 63) / 64)) / 256.0), s = (double)((red + 31) / 32);
-    best = 0.85 * (3.0 + r * (0.642 * s + 1.039) + 0.09 * s);
+    best = layout == NCHW ? 0.85 * (4.0 + r * (1.17 * s + 1.0) + 0.09 * s)
+                          : 0.85 * (3.0 + r * (0.642 * s + 1.039) + 0.09 * s);
   }
   const double s = (double)(((red + 15) / 16 + 7) / 8);
   for (const Fit& f : fits) {
     const long long wg = ((m + 16 * f.fm - 1) / (16 * f.fm)) * ((k + 16 * f.fn - 1) / (16 * f.fn));
-    const double t = 3.0 + std::max(1.0, (double)wg / 256.0) * (f.step * s + f.tile);
+    const double t = 3.0 + std::max(1.0, (double)wg / 256.0) * (f.step * (layout == NCHW ? 1.65 : 1.0) * s + f.tile);
     if (t < best) {
       best = t;
       pick = f.fm * 8 + f.fn;
@@ -333,7 +368,8 @@ bool ksplit_applicable(int dtype, int layout, int n, int c, int h, int w, int r,
                        int c2) {
   const long long p = (h + 2 * pad - r) / stride + 1, q = (w + 2 * pad - s) / stride + 1, es = dtype == 0 ? 4 : 2;
   const long long c8 = (c + 7) / 8 * 8, kp = (k + 7) / 8 * 8, k2 = (c2 + 7) / 8 * 8;
-  if (!(layout == NC8 || (layout == NHWC && c % 8 == 0 && c2 % 8 == 0))) return false;
+  if (!(layout == NC8 || (layout == NHWC && c % 8 == 0 && c2 % 8 == 0) || (layout == NCHW && dtype == 0 && c2 == 0)))
+    return false;
   // exact fp32 index divisions (pixels, reduction chunks) and 32-bit byte
   // offsets into every tensor
   const long long nch = (long long)r * s * (c8 * es / 16);
@@ -348,7 +384,11 @@ static void ks_go(KsArgs a, bool k1, hipStream_t st) {
   a.tiles_m = (a.M + 16 * FM - 1) / (16 * FM);
   a.tiles_n = (a.Ng + 16 * FN - 1) / (16 * FN);
   const dim3 grid(a.tiles_m * a.tiles_n), block(64 * NW);
-  if (a.x2) {
+  if constexpr (L == NCHW) {
+    check(!a.x2, "wave-split kernel: no projected shortcut in NCHW");
+    if (k1) SN_LAUNCH((conv_ksplit_kernel<T, L, FM, FN, NW, D, true, false>), grid, block, 0, st, a);
+    else SN_LAUNCH((conv_ksplit_kernel<T, L, FM, FN, NW, D, false, false>), grid, block, 0, st, a);
+  } else if (a.x2) {
     if (k1) SN_LAUNCH((conv_ksplit_kernel<T, L, FM, FN, NW, D, true, true>), grid, block, 0, st, a);
     else SN_LAUNCH((conv_ksplit_kernel<T, L, FM, FN, NW, D, false, true>), grid, block, 0, st, a);
   } else {
@@ -374,7 +414,7 @@ void conv_ksplit(int dtype, int fm, int fn, int nw, const ConvArgs& c, hipStream
             c.yd.w == (c.xd.w + 2 * c.pad - c.s) / c.stride + 1 &&
             ksplit_applicable(dtype, c.xd.layout, c.xd.n, c.xd.c, c.xd.h, c.xd.w, c.r, c.s, c.stride, c.pad, c.yd.c,
                               c.x2 ? c.x2d.c : 0),
-        "wave-split kernel: one channel-vector layout, C % 8 == 0 in NHWC, tensors below 2 GiB");
+        "wave-split kernel: one layout, C % 8 == 0 in NHWC, fp32 in NCHW, tensors below 2 GiB");
   const int es = dtype == 0 ? 4 : 2, ce = 16 / es;
   KsArgs a{};
   a.x = c.x;
@@ -431,6 +471,7 @@ void conv_ksplit(int dtype, int fm, int fn, int nw, const ConvArgs& c, hipStream
   const bool nc8 = c.xd.layout == NC8;
   if (dtype == 0) {
     if (nc8) ks_tile<float, NC8>(fm, fn, nw, a, k1, st);
+    else if (c.xd.layout == NCHW) ks_tile<float, NCHW>(fm, fn, nw, a, k1, st);
     else ks_tile<float, NHWC>(fm, fn, nw, a, k1, st);
   } else if (dtype == 1) {
     if (nc8) ks_tile<f16, NC8>(fm, fn, nw, a, k1, st);

@@ -1380,8 +1380,9 @@ static void igemm_dispatch(int dtype, int param, const ConvArgs& c, hipStream_t 
     // fp32 has one parameter; the tile follows from the size
     if (c.wks && ksplit_applicable(dtype, c.xd.layout, c.xd.n, c.xd.c, c.xd.h, c.xd.w, c.r, c.s, c.stride, c.pad,
                                    c.yd.c, c.x2 ? c.x2d.c : 0)) {
-      const int t = ksplit_pick_f32((long long)c.yd.n * c.yd.h * c.yd.w, c.yd.c,
-                                    (long long)c.r * c.s * c.xd.c + (c.x2 ? c.x2d.c : 0), !c.x2);
+      const int cc = c.xd.layout == NCHW ? (c.xd.c + 7) / 8 * 8 : c.xd.c;
+      const int t = ksplit_pick_f32(c.xd.layout, (long long)c.yd.n * c.yd.h * c.yd.w, c.yd.c,
+                                    (long long)c.r * c.s * cc + (c.x2 ? c.x2d.c : 0), !c.x2);
       if (t) {
         check(!c.res || !c.x2, "a projected shortcut replaces the residual");
         conv_ksplit(dtype, t / 8, t % 8, 8, c, st);

@@ -204,7 +204,7 @@ bool stream1x1_takes_projection(int layout, int c, int cs, int n, int h, int w, 
 void conv1x1_stream(int dtype, int cc, int bm, int bn, int pd, const ConvArgs& a, hipStream_t st, int occ = 1);
 // Implicit GEMM with the reduction split over a workgroup's waves, for launches
 // bound by latency (see conv_ksplit.hip; NHWC with C % 8 == 0 or NC8HW8, every
-// type; c2 > 0: with a projected shortcut of c2 channels).  Instantiated
+// type; NCHW, fp32, without a projected shortcut; c2 > 0: with a projected shortcut of c2 channels).  Instantiated
 // tiles (FM, FN, NW, D): 16 FM pixels x 16 FN channels, NW waves, D reduction
 // steps in flight per wave; in 16-bit types each is one implicit-GEMM routine
 // parameter, in fp32 the one routine takes a tile by size (ksplit_pick_f32).
@@ -216,10 +216,10 @@ void conv1x1_stream(int dtype, int cc, int bm, int bn, int pd, const ConvArgs& a
   X(4, 4, 8, 2)
 bool ksplit_applicable(int dtype, int layout, int n, int c, int h, int w, int r, int s, int stride, int pad, int k,
                        int c2);
-// the fp32 implicit GEMM's tile for m output pixels, k output channels and
-// a reduction of red: FM * 8 + FN of a wave-split tile, or 0 for the LDS
+// the fp32 implicit GEMM's tile in the layout for m output pixels, k output channels and
+// a reduction of red (NCHW: over the channels rounded up to 8): FM * 8 + FN of a wave-split tile, or 0 for the LDS
 // tile (lds_ok: whether that one can run the layer)
-int ksplit_pick_f32(long long m, int k, long long red, bool lds_ok);
+int ksplit_pick_f32(int layout, long long m, int k, long long red, bool lds_ok);
 // the kernel's filter order: kp rows of row_bytes (a multiple of 16) as blocks
 // of 16 rows x 4 chunks of 16 bytes, each 1 KB in lane order
 size_t ksplit_packed_bytes(int kp, size_t row_bytes);

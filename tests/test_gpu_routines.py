@@ -559,3 +559,20 @@ def test_gap_planes_edges(dtype, shape):
         out = from_dev(run_routine(g, 0, t), dtype).reshape(ref.shape)
         assert err(out, ref, dtype) <= TOL[dtype] * 0.1
     g.close()
+
+
+@pytest.mark.parametrize("case", [(2, 3, 9, 7, 16, 3, 1, 1), (2, 5, 6, 6, 10, 1, 2, 0), (1, 7, 11, 5, 33, 5, 2, 2)])
+def test_wave_split_nchw_reads_no_neighbour(case):
+    """fp32 NCHW: the channels past C that fill a chunk are not the next
+    image's: infinities there leave this image's outputs as they were."""
+    n, c, h, w, k, r, st, pad = case
+    layer = {"type": "conv", "in": [0], "k": k, "r": r, "s": r, "stride": st, "pad": pad, "groups": 1, "act": "none"}
+    x = random_tensor((n, c, h, w), "f32", seed=31)
+    wt = random_tensor((k, c, r, r), "f32", seed=32, dist="normal", scale=np.sqrt(2 / (c * r * r)))
+    b = random_tensor((k,), "f32", seed=33, scale=0.1)
+    ref = oracle_layer(layer, x, wt, b, "f32")
+    x[1:] = np.inf
+    g = single_layer_graph("f32", (n, c, h, w), layer, wt, b, layouts=["NCHW"], algos=["igemm"])
+    out = from_dev(run_routine(g, 0, to_dev(x, "f32")), "f32")
+    assert err(out[:1], ref[:1], "f32") <= TOL["f32"]
+    g.close()
