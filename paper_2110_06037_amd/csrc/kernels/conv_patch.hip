@@ -71,6 +71,85 @@ struct PatchArgs {
 template <int V>
 using IC = std::integral_constant<int, V>;
 
+// Stores a tile whose outputs are staged in LDS rows (one per valid pixel) of
+// OP bytes, BN channels from n0, its pixels GEMM rows from mbase on; ROWS
+// rows at most.  See the end of the kernel below.
+template <typename T, int L, int BN, int OP, int ROWS>
+__device__ __forceinline__ void patch_store(const PatchArgs& a, const char* smem, int n0, int valid, int mbase,
+                                            int tid) {
+  constexpr int NT = 512;
+  const int PQ = a.P * a.Q;
+  T* __restrict__ y = reinterpret_cast<T*>(a.y);
+  const __amdgpu_buffer_rsrc_t ry = make_rsrc(y, a.y_elems * 2);
+  constexpr int CPX = BN / 8;  // 16-byte chunks per pixel
+  const bool vec8 = L == NC8 || a.Ks % 8 == 0;
+  // chunk q of the tile: its staged outputs (LDS byte) and element offset
+  auto chunk = [&](int q, int& lds, unsigned& e, int& n) {
+    int ml, c8;
+    if constexpr (L == NC8) {
+      c8 = q / valid;
+      ml = q - c8 * valid;
+    } else {
+      ml = q / CPX;
+      c8 = q - ml * CPX;
+    }
+    n = n0 + c8 * 8;
+    lds = ml * OP + c8 * 16;
+    const int m = mbase + ml;
+    if constexpr (L == NC8) {
+      const int img = sdiv(m, a.inv_pq), pq = m - img * PQ;
+      e = (unsigned)(((img * (a.Ks >> 3) + (n >> 3)) * PQ + pq) * 8);
+    } else {
+      e = (unsigned)(m * a.Ks + n);
+    }
+  };
+  if (a.res) {
+    // the addition: all of a thread's residual chunks are loaded before the
+    // first is used (out-of-range offsets past the tile load and store
+    // nothing); the host admits whole 16-byte chunks only
+    constexpr int NC = (ROWS * CPX + NT - 1) / NT;
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, a.y_elems * 2);
+    u32x4 rv[NC];
+    unsigned off[NC];
+    int ls[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int q = tid + c * NT;
+      int n;
+      unsigned e;
+      chunk(q < valid * CPX ? q : 0, ls[c], e, n);
+      off[c] = q < valid * CPX && n < a.Ng ? e * 2u : kOOB;
+      rv[c] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[c], 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      T o[8], r[8];
+      __builtin_memcpy(o, smem + ls[c], 16);
+      __builtin_memcpy(r, &rv[c], 16);
+#pragma unroll
+      for (int v = 0; v < 8; ++v) o[v] = from_f<T>(act_f(to_f(o[v]) + to_f(r[v]), a.act));
+      u32x4 pk;
+      __builtin_memcpy(&pk, o, 16);
+      __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[c], 0, 0);
+    }
+    return;
+  }
+  for (int q = tid; q < valid * CPX; q += NT) {
+    int lds, n;
+    unsigned e;
+    chunk(q, lds, e, n);
+    if (n >= a.Ng) continue;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(smem + lds);
+    if (vec8 && n + 8 <= a.Ng) {
+      __builtin_amdgcn_raw_buffer_store_b128(v, ry, (int)(e * 2u), 0, 0);
+    } else {
+      T o[8];
+      __builtin_memcpy(o, &v, 16);
+      for (int t = 0; t < 8 && n + t < a.Ng; ++t) y[e + t] = o[t];
+    }
+  }
+}
+
 // FMT: MFMA row blocks (16 pixels) per tile; BN output channels; PWT patch
 // row pitch (a power of two >= Q + 2); the 8 waves form TG tap groups of
 // WM x WN waves (group g runs taps [9g/TG, 9(g+1)/TG) of every step on the
@@ -332,78 +411,190 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
     }
   }
   __syncthreads();
-  const int valid = imgs * rows * a.Q;
-  const int mbase = img0 * a.P * a.Q + row0 * a.Q;
-  const int PQ = a.P * a.Q;
-  T* __restrict__ y = reinterpret_cast<T*>(a.y);
-  const __amdgpu_buffer_rsrc_t ry = make_rsrc(y, a.y_elems * 2);
-  constexpr int CPX = BN / 8;  // 16-byte chunks per pixel
-  const bool vec8 = L == NC8 || a.Ks % 8 == 0;
-  // chunk q of the tile: its staged outputs (LDS byte) and element offset
-  auto chunk = [&](int q, int& lds, unsigned& e, int& n) {
-    int ml, c8;
-    if constexpr (L == NC8) {
-      c8 = q / valid;
-      ml = q - c8 * valid;
-    } else {
-      ml = q / CPX;
-      c8 = q - ml * CPX;
+  patch_store<T, L, BN, OP, FMT * 16>(a, smem, n0, imgs * rows * a.Q, img0 * a.P * a.Q + row0 * a.Q, tid);
+}
+
+// The same convolution (stride 1, row-aligned blocks, a tile's rows of one
+// image) for layers with enough tiles to fill the chip at 128 output channels.
+// What bounds the kernel above at its largest tile (7 x 2 blocks per wave) is the
+// LDS: 9 operand reads for 14 MFMAs, 72 KB per tap against the 56 KB that the
+// matrix cores' time admits, since its stage holds all 9 taps' filter rows and
+// leaves room for 64 channels.  Here only one tap row's filter rows (3 taps, 24 KB)
+// are a stage, three of them rotating, beside two patch buffers: 144 KB hold a
+// tile of 128 channels, each wave has 7 x 4 blocks (11 reads for 28 MFMAs),
+// and each input element is read by half as many workgroups.
+// Against the fastest other routine in fp16 at batch 32 (a library product of 8192^3
+// reaches 1.15 PFLOP/s here): 256 channels at 56 x 56, 111.4 -> 106.3 us (1.11 PFLOP/s);
+// 512 at 28 x 28, 119.7 -> 100.2 (1.18); 256 -> 512 there, 64.4 -> 52.9.  Below one
+// tile per CU it loses (128 at 28 x 28, 11.4 against 22.3), and selection takes the
+// others.  Reading the next tap row's first operands before its barrier needs more
+// registers than there are (50 spilled, 188 us).
+// FMT = 28 row blocks, 4 x 2 waves; the tile's row blocks are consecutive LDS
+// rows, so all operand addresses are three registers plus immediates.
+template <typename T, int L, int FMT, int BN, int PWT, int PROWS>
+__global__ __launch_bounds__(512, 2) void conv3x3_patch_wide_kernel(PatchArgs a) {
+  static_assert(sizeof(T) == 2 && L != NCHW, "16-bit channel-vector layouts only");
+  constexpr int NWV = 8, WM = 4, WN = 2, RB = 64;
+  constexpr int LPW = PWT == 32 ? 5 : 6;
+  static_assert(PWT == 1 << LPW && FMT % WM == 0 && FMT * 16 % PWT == 0, "whole patch rows, whole waves");
+  constexpr int FMW = FMT / WM, FNW = BN / WN / 16;
+  constexpr int NPL = (PROWS / 16 + NWV - 1) / NWV;  // patch load instructions per wave
+  constexpr int NFL = 3 * BN / 16 / NWV;             // a tap row's filter load instructions per wave
+  static_assert(NFL * NWV * 16 == 3 * BN && PROWS % 16 == 0, "whole load instructions");
+  constexpr int PB = NPL * NWV * 1024, FB = NFL * NWV * 1024;
+  constexpr int OP = BN * 2 + 16;  // staging row bytes
+  constexpr int SM = 2 * PB + 3 * FB;
+  static_assert(SM <= 160 * 1024 && FMT * 16 * OP <= SM, "LDS capacity");
+  // dropped columns read up to two rows past the patch: still this memory
+  static_assert((FMT * 16 + 2 + 2 * PWT) * RB <= PB + 3 * FB, "operand reads stay in the tile's LDS");
+  __shared__ __attribute__((aligned(1024))) char smem[SM];
+  lds_char* const sl = (lds_char*)smem;
+  auto swz = [](int row) { return (row >> 1) & 3; };
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  int mt, nt;
+  tile_of(blockIdx.x, a.tiles_m, a.tiles_n, mt, nt);
+  const int img = fdiv(mt, a.fd_ti_tiles), rt = mt - img * a.tiles_img;
+  const int row0 = rt * a.TR;
+  const int rows = min(a.TR, a.P - row0);
+  const int n0 = nt * BN;
+  const int KT = a.CB / 4;
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, a.x_elems * 2);
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.w, a.w_elems * 2);
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(a.bias, (long long)a.Ng * 4);
+
+  // sums start at the bias (4 consecutive channels per lane and block)
+  f32x4 acc[FMW][FNW];
+#pragma unroll
+  for (int j = 0; j < FNW; ++j) {
+    const int n = n0 + (wn * FNW + j) * 16 + (lane >> 4) * 4;
+    f32x4 b;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      b[v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (n + v) * 4, 0, 0));
+#pragma unroll
+    for (int i = 0; i < FMW; ++i) acc[i][j] = b;
+  }
+
+  // load instruction q = wave + 8 i fills LDS rows [16 q, 16 q + 16), this lane
+  // row 16 q + lane / 4, physical chunk lane % 4
+  unsigned poff[NPL], foff[NFL];
+  const int lrow = lane >> 2;
+#pragma unroll
+  for (int i = 0; i < NPL; ++i) {
+    const int row = 16 * (wave + NWV * i) + lrow, lcp = (lane & 3) ^ swz(row);
+    const int ph = row >> LPW, pw = row & (PWT - 1);
+    const int h = row0 - 1 + ph, ww = pw - 1;
+    const bool ok = ph < a.PH && (unsigned)h < (unsigned)a.H && (unsigned)ww < (unsigned)a.W;
+    unsigned e;
+    if constexpr (L == NC8)
+      e = __umul24(__umul24(img, a.CB) + lcp, a.HW8) + __umul24(h, a.W8) + ww * 8;
+    else
+      e = __umul24(__umul24(__umul24(img, a.H) + h, a.W) + ww, a.Cs) + lcp * 8;
+    poff[i] = ok ? e * 2u : kOOB;
+  }
+#pragma unroll
+  for (int i = 0; i < NFL; ++i) {
+    const int row = 16 * (wave + NWV * i) + lrow, lcp = (lane & 3) ^ swz(row);
+    const int s = row / BN, kch = n0 + row % BN;
+    foff[i] = kch < a.Ng ? (__umul24(kch, a.Kred) + __umul24(s, a.C8) + lcp * 8) * 2u : kOOB;
+  }
+  const int xstep = L == NC8 ? 4 * a.HW8 * 2 : RB;
+  auto issue_patch = [&](auto BC, int kt) {
+    constexpr int B = decltype(BC)::value;
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) dma16(rx, sl + B * PB + (wave + NWV * i) * 1024, poff[i], kt * xstep);
+  };
+  auto issue_filter = [&](auto RC, int kt) {
+    constexpr int R = decltype(RC)::value;
+#pragma unroll
+    for (int i = 0; i < NFL; ++i)
+      dma16(rw, sl + 2 * PB + R * FB + (wave + NWV * i) * 1024, foff[i], (R * 3 * a.C8 + kt * 32) * 2);
+  };
+  issue_patch(IC<0>{}, 0);
+  issue_filter(IC<0>{}, 0);
+  issue_filter(IC<1>{}, 0);
+
+  // operand chunk of this lane: patch row (wm FMW + i) 16 + lane % 16 + s + r PWT,
+  // filter row s BN + (wn FNW + j) 16 + lane % 16; multiples of 16 rows keep the swizzle
+  int aoff[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int r = wm * FMW * 16 + (lane & 15) + c;
+    aoff[c] = (r << 6) | (((lane >> 4) ^ swz(r)) << 4);
+  }
+  const int boff = 2 * PB + (wn * FNW * 16 + (lane & 15)) * RB + (((lane >> 4) ^ swz(lane & 15)) << 4);
+
+  typedef typename Mfma<T>::frag frag;
+  // tap row R of step kt, the step's patch in buffer B.  Before it: its filter
+  // rows (and at R = 0 the patch) have landed, which leaves only what was
+  // issued after them in flight, and every wave is past the tap row before, whose
+  // buffers the next loads take.
+  auto sub = [&](auto BC, auto RC, int kt) {
+    constexpr int B = decltype(BC)::value, R = decltype(RC)::value;
+    const bool more = kt + 1 < KT;
+    if constexpr (R == 0) wait_vmcnt<NFL>();
+    else if (more) wait_vmcnt<NPL + NFL>();
+    else wait_vmcnt<R == 1 ? NFL : 0>();
+    dma_barrier();
+    if constexpr (R == 0) {
+      issue_filter(IC<2>{}, kt);
+      if (more) issue_patch(IC<(B ^ 1)>{}, kt + 1);
+    } else if (more) {
+      issue_filter(IC<R - 1>{}, kt + 1);
     }
-    n = n0 + c8 * 8;
-    lds = ml * OP + c8 * 16;
-    const int m = mbase + ml;
-    if constexpr (L == NC8) {
-      const int img = sdiv(m, a.inv_pq), pq = m - img * PQ;
-      e = (unsigned)(((img * (a.Ks >> 3) + (n >> 3)) * PQ + pq) * 8);
-    } else {
-      e = (unsigned)(m * a.Ks + n);
+    frag fa[2][FMW], fb[2][FNW];
+    auto load = [&](int s, int b) {
+#pragma unroll
+      for (int j = 0; j < FNW; ++j)
+        fb[b][j] = *reinterpret_cast<const frag*>(smem + boff + R * FB + (s * BN + j * 16) * RB);
+#pragma unroll
+      for (int i = 0; i < FMW; ++i)
+        fa[b][i] = *reinterpret_cast<const frag*>(smem + aoff[s] + B * PB + (i * 16 + R * PWT) * RB);
+    };
+    load(0, 0);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      if (s < 2) load(s + 1, (s + 1) & 1);
+      // keep the next tap's reads ahead of this tap's MFMAs
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < FMW; ++i)
+#pragma unroll
+        for (int j = 0; j < FNW; ++j) acc[i][j] = Mfma<T>::run(fb[s & 1][j], fa[s & 1][i], acc[i][j]);
     }
   };
-  if (a.res) {
-    // the addition: all of a thread's residual chunks are loaded before the
-    // first is used (out-of-range offsets past the tile load and store
-    // nothing); the host admits whole 16-byte chunks only
-    constexpr int NC = (FMT * 16 * CPX + NWV * 64 - 1) / (NWV * 64);
-    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, a.y_elems * 2);
-    u32x4 rv[NC];
-    unsigned off[NC];
-    int ls[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int q = tid + c * NWV * 64;
-      int n;
-      unsigned e;
-      chunk(q < valid * CPX ? q : 0, ls[c], e, n);
-      off[c] = q < valid * CPX && n < a.Ng ? e * 2u : kOOB;
-      rv[c] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[c], 0, 0);
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      T o[8], r[8];
-      __builtin_memcpy(o, smem + ls[c], 16);
-      __builtin_memcpy(r, &rv[c], 16);
-#pragma unroll
-      for (int v = 0; v < 8; ++v) o[v] = from_f<T>(act_f(to_f(o[v]) + to_f(r[v]), a.act));
-      u32x4 pk;
-      __builtin_memcpy(&pk, o, 16);
-      __builtin_amdgcn_raw_buffer_store_b128(pk, ry, (int)off[c], 0, 0);
-    }
-    return;
+  for (int kt = 0; kt < KT; kt += 2) {
+    sub(IC<0>{}, IC<0>{}, kt);
+    sub(IC<0>{}, IC<1>{}, kt);
+    sub(IC<0>{}, IC<2>{}, kt);
+    if (kt + 1 >= KT) break;
+    sub(IC<1>{}, IC<0>{}, kt + 1);
+    sub(IC<1>{}, IC<1>{}, kt + 1);
+    sub(IC<1>{}, IC<2>{}, kt + 1);
   }
-  for (int q = tid; q < valid * CPX; q += NWV * 64) {
-    int lds, n;
-    unsigned e;
-    chunk(q, lds, e, n);
-    if (n >= a.Ng) continue;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(smem + lds);
-    if (vec8 && n + 8 <= a.Ng) {
-      __builtin_amdgcn_raw_buffer_store_b128(v, ry, (int)(e * 2u), 0, 0);
-    } else {
-      T o[8];
-      __builtin_memcpy(o, &v, 16);
-      for (int t = 0; t < 8 && n + t < a.Ng; ++t) y[e + t] = o[t];
+
+  // epilogue as above: outputs to LDS rows of their place among the tile's
+  // pixels (columns past Q dropped), then 16-byte chunks
+  const ActClamp ac = act_clamp(a.res ? ACT_NONE : a.act);
+  __syncthreads();  // every wave is done with the stages
+#pragma unroll
+  for (int i = 0; i < FMW; ++i) {
+    const int m = (wm * FMW + i) * 16 + (lane & 15), pr = m >> LPW, pc = m & (PWT - 1);
+    if (pc >= a.Q || pr >= rows) continue;
+    const int ml = pr * a.Q + pc;
+#pragma unroll
+    for (int j = 0; j < FNW; ++j) {
+      T o[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[v] = from_f<T>(__builtin_amdgcn_fmed3f(acc[i][j][v], ac.lo, ac.hi));
+      __builtin_memcpy(smem + ml * OP + ((wn * FNW + j) * 16 + (lane >> 4) * 4) * 2, o, 8);
     }
   }
+  __syncthreads();
+  patch_store<T, L, BN, OP, FMT * 16>(a, smem, n0, rows * a.Q, img * a.P * a.Q + row0 * a.Q, tid);
 }
 
 // ------------------------------------------------------------------ host
@@ -414,6 +605,7 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
 static bool patch_tiling(PatchArgs& a, int fmt, int pwt, int prows, int sd, int ra = 0) {
   const int maxpx = fmt * 16;
   if (a.Q > maxpx || (a.Q - 1) * sd + 3 > pwt || (ra && sd != 1)) return false;
+  if (ra == 2 && a.P * pwt < maxpx) return false;  // the wide kernel: rows of one image, no row block unused
   if (ra && 2 * a.Q <= pwt) return false;  // most virtual columns would be dropped
   // row-aligned tiles count an output row as pwt (virtual) pixels
   const int rowpx = ra ? pwt : a.Q;
@@ -498,6 +690,16 @@ static void patch_go(PatchArgs a, hipStream_t st) {
             a);
 }
 
+template <typename T, int L, int FMT, int BN, int PWT, int PROWS>
+static void patch_wide_go(PatchArgs a, hipStream_t st) {
+  check(patch_tiling(a, FMT, PWT, PROWS, 1, 2) && a.TI == 1, "output does not fit the wide patch tile");
+  check(a.CB % 4 == 0, "patch kernel needs C % 32 == 0");
+  check(a.x_elems * 2 < (long long)kOOB && a.w_elems * 2 < (long long)kOOB,
+        "tensor too large for 32-bit buffer offsets");
+  a.tiles_n = (a.Ng + BN - 1) / BN;
+  SN_LAUNCH((conv3x3_patch_wide_kernel<T, L, FMT, BN, PWT, PROWS>), dim3(a.tiles_m * a.tiles_n), dim3(512), 0, st, a);
+}
+
 static long long patch_key(int fmt, int bn, int pwt, int wm, int wn, int tg, int stg, int prows, int sd, int occ,
                            int ra) {
   return (((((((((fmt * 1000LL + bn) * 100 + pwt) * 10 + wm) * 10 + wn) * 10 + tg) * 10 + stg) * 10000 + prows) * 10 +
@@ -527,6 +729,12 @@ static void patch_layout(const PatchCfg& c, const PatchArgs& a, hipStream_t st) 
     patch_go<T, L, FMT_, BN_, PWT_, WM_, WN_, TG_, ST_, PROWS_, 1, OCC_, true>(a, st);  \
     return;                                                                            \
   }
+#define PGOW(FMT_, BN_, PWT_, PROWS_)                                                  \
+  if (c.ra == 2 && c.fmt == FMT_ && c.bn == BN_ && c.pwt == PWT_ && c.prows == PROWS_) { \
+    patch_wide_go<T, L, FMT_, BN_, PWT_, PROWS_>(a, st);                               \
+    return;                                                                            \
+  }
+  PATCHW_CONFIGS(PGOW)
   PATCH_CONFIGS(PGO)
   PATCH2_CONFIGS(PGO2)
   PATCH_OCC2_CONFIGS(PGOO2)
@@ -535,6 +743,7 @@ static void patch_layout(const PatchCfg& c, const PatchArgs& a, hipStream_t st) 
 #undef PGO2
 #undef PGOO2
 #undef PGORA
+#undef PGOW
   check(false, "patch tile not instantiated");
 }
 

@@ -1112,6 +1112,11 @@ static const IgCfg kIg16[] = {
 #define SN_KSPLIT_IG(FM, FN, NW, D) {16 * FM, 16 * FN, 32, 0, D, 5, 1, 1, 0, {}, NW},
     KSPLIT_CONFIGS(SN_KSPLIT_IG)
 #undef SN_KSPLIT_IG
+    // wide 3x3 patch kernel (appended)
+#define SN_PATCHW_IG(FMT, BN, PWT, PROWS) \
+  {16 * FMT, BN, 32, 0, 0, 2, 4, 3, 0, {FMT, BN, PWT, 4, 2, 1, 3, PROWS, 1, 1, 2}},
+    PATCHW_CONFIGS(SN_PATCHW_IG)
+#undef SN_PATCHW_IG
 };
 static const IgCfg kIg32[] = {{64, 64, 32, 0, 2}};
 

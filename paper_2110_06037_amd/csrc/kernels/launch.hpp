@@ -108,7 +108,7 @@ struct PatchCfg {
   int fmt, bn, pwt, wm, wn, tg, st, prows;  // one PATCH_CONFIGS tuple
   int sd = 1;                               // convolution stride
   int occ = 1;                              // workgroups per CU the tile is sized for
-  int ra = 0;                               // 1: row-aligned row blocks (stride 1)
+  int ra = 0;                               // 1: row-aligned row blocks (stride 1); 2: the wide kernel
 };
 // Instantiated patch tiles (FMT, BN, PWT, WM, WN, TG, ST, PROWS): FMT row
 // blocks of 16 output pixels, BN output channels, patch row pitch PWT, 8
@@ -149,6 +149,11 @@ struct PatchCfg {
   X(14, 64, 32, 4, 2, 1, 2, 288, 1) \
   X(8, 64, 16, 4, 1, 2, 2, 288, 1)  \
   X(8, 32, 16, 4, 1, 2, 2, 160, 2)
+// Tiles of the wide patch kernel (stride 1, row-aligned, the filter streamed by
+// tap rows; FMT, BN, PWT, PROWS)
+#define PATCHW_CONFIGS(X) \
+  X(28, 128, 64, 576)     \
+  X(28, 128, 32, 512)
 bool patch_applicable(int layout, int c, int h, int w, int r, int s, int stride, int pad, int n,
                       int fmt, int pwt, int prows, int sd, int ra = 0);
 void conv_patch(int dtype, const PatchCfg& cfg, const ConvArgs& a, hipStream_t st);

@@ -576,3 +576,30 @@ def test_wave_split_nchw_reads_no_neighbour(case):
     out = from_dev(run_routine(g, 0, to_dev(x, "f32")), "f32")
     assert err(out[:1], ref[:1], "f32") <= TOL["f32"]
     g.close()
+
+
+# (N, C, H, W, K): one and odd numbers of 32-channel steps, ragged last row
+# tiles, the widest rows, images of exactly one tile, ragged channel tiles,
+# padded channels (NC8HW8 only)
+WIDE_PATCH_CASES = [(2, 32, 56, 56, 128), (1, 64, 50, 62, 136), (3, 160, 7, 40, 72), (2, 96, 28, 28, 200),
+                    (2, 64, 14, 20, 128), (1, 32, 29, 30, 65), (1, 30, 20, 25, 100), (1, 128, 61, 33, 256)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("case", WIDE_PATCH_CASES)
+def test_wide_patch_edges(dtype, case):
+    """The wide 3x3 patch kernel (parameters 111 and 112)."""
+    n, c, h, w, k = case
+    layer = {"type": "conv", "in": [0], "k": k, "r": 3, "s": 3, "stride": 1, "pad": 1, "groups": 1, "act": "relu"}
+    x = random_tensor((n, c, h, w), dtype, seed=61)
+    wt = random_tensor((k, c, 3, 3), dtype, seed=62, dist="normal", scale=np.sqrt(2 / (9 * c)))
+    b = random_tensor((k,), "f32", seed=63, scale=0.1)
+    ref = oracle_layer(layer, x, wt, b, dtype)
+    g = single_layer_graph(dtype, (n, c, h, w), layer, wt, b, algos=["igemm"])
+    mine = [rt for rt in g.routines(1) if rt["param"] >= 111]
+    assert {rt["layout"] for rt in mine} == ({1, 2} if c % 8 == 0 else {2})
+    xd = to_dev(x, dtype)
+    for rt in mine:
+        out = from_dev(run_routine(g, rt["id"], xd), dtype)
+        assert err(out, ref, dtype) <= TOL[dtype], (rt["name"], err(out, ref, dtype))
+    g.close()
