@@ -61,6 +61,9 @@ struct Step {
   k::TDesc outd{};
   BufRef ws;
   size_t ws_bytes = 0;
+  int adapt = -1;  // the launch reads the converter's source itself: index of the converter's
+                   // step, and with the layer's own after it what to run when the source is
+                   // not 4-byte aligned
   int run = -1;  // layer whose routine the step launches (with `layer`'s addition when they differ)
 };
 
@@ -820,6 +823,27 @@ static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share, bool fuse, 
   std::sort(order.begin(), order.end(), [&](int a, int b) {
     return bufs[a].bytes != bufs[b].bytes ? bufs[a].bytes > bufs[b].bytes : a < b;
   });
+  // adapts that the convolution they feed makes while it reads: NCHW images into
+  // the small-channel kernel (their converted copy, which nothing else reads then,
+  // was 9.6 MB written and read again at 32 x 3 x 224 x 224)
+  std::vector<int> adapt_of(n, -1);
+  if (fuse && !g.opt_keep) {
+    for (int i = 1; i < n; ++i) {
+      const Layer& L = g.layers[i];
+      const int a = P->first_step[i];
+      if (gone[i] || L.type != SN_LAYER_CONV2D || L.d.groups != 1 || L.inputs.size() != 1 || P->steps[a].type != 0)
+        continue;
+      const Routine& r = L.routines[g.path[i]];
+      const Step& c = P->steps[a];
+      if (r.algo != SN_ALGO_IGEMM || c.sd.layout != SN_NCHW || c.dd.layout != SN_NHWC || c.sdt != c.ddt ||
+          !k::igemm_param_reads_nchw(r.dtype, r.param, c.sd.h, c.sd.w, L.d.r, L.d.s, L.d.stride, L.d.pad))
+        continue;
+      int readers = 0;  // layers whose step reads this converted copy
+      for (const Step& s : P->steps)
+        for (int q = 0; s.type == 1 && q < s.n_in; ++q) readers += s.in[q].kind == 0 && s.in[q].off == c.dst.off;
+      if (readers == 1) adapt_of[i] = a;
+    }
+  }
   std::vector<int> placed;
   size_t total = 0;
   auto held = [&](const Buf& b) { return (int64_t)b.last + hold; };
@@ -854,8 +878,18 @@ static std::unique_ptr<Plan> plan_layout(const Graph& g, bool share, bool fuse, 
   P->layer_out = out_ref;
   for (BufRef& r : P->layer_out) resolve(r);
   P->arena_bytes = std::max<size_t>(total, 256);
-  for (const Step& s : P->steps) {
+  for (size_t si = 0; si < P->steps.size(); ++si) {
+    const Step& s = P->steps[si];
     if (s.type == 1 && gone[s.layer]) continue;
+    if (adapt_of[s.layer] == (int)si) continue;
+    if (adapt_of[s.layer] >= 0 && s.type == 1) {
+      Step f = s;
+      f.adapt = adapt_of[s.layer];
+      f.in[0] = P->steps[f.adapt].src;
+      f.ind[0] = P->steps[f.adapt].sd;
+      P->fused.push_back(f);
+      continue;
+    }
     if (s.type == 1 && conv_of[s.layer] >= 0) {
       const int c = conv_of[s.layer];
       Step f = P->steps[P->last_step[c]];
@@ -919,6 +953,11 @@ static void enqueue_step(const Graph& g, const Plan& P, char* base, const Step& 
     if (r.kind == 2) return d_out[r.idx];
     return base + r.off;
   };
+  if (s.adapt >= 0 && reinterpret_cast<uintptr_t>(ptr(s.in[0])) % 4) {
+    enqueue_step(g, P, base, P.steps[s.adapt], d_in, d_out, st);
+    enqueue_step(g, P, base, P.steps[s.adapt + 1], d_in, d_out, st);
+    return;
+  }
   if (s.type == 0) {
     k::convert_cast(s.sdt, ptr(s.src), s.sd, s.ddt, ptr(s.dst), s.dd, st);
   } else {

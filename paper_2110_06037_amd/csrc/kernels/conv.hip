@@ -73,6 +73,12 @@ bool igemm_param_fuses_add(int dtype, int param, int layout, int k) {
   return g.dma == 5 || (g.dma == 2 && (layout == NC8 || k % 8 == 0));
 }
 
+bool igemm_param_reads_nchw(int dtype, int param, int h, int w, int r, int s, int stride, int pad) {
+  if (dtype == 0 || param < 0 || param >= igemm_num_params(dtype) || kIg16[param].dma != 3) return false;
+  const IgCfg& g = kIg16[param];
+  return smallc_reads_nchw(h, w, r, s, stride, pad, g.bm / 16, g.ppx, g.gmax);
+}
+
 bool igemm_param_takes_projection(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
                                   int stride, int pad, int k, int c2) {
   if (param < 0 || param >= igemm_num_params(dtype)) return false;

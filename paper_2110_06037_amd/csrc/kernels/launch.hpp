@@ -94,6 +94,9 @@ bool igemm_param_takes_residual(int dtype, int param, int layout, int k);
 // whether the tile configuration also adds it after rounding its sum
 // (ConvArgs::round_sum: a convolution and the ADD layer after it in one launch)
 bool igemm_param_fuses_add(int dtype, int param, int layout, int k);
+// whether the tile configuration, valid for an NHWC layer, also reads its input
+// from NCHW planes that start at a multiple of 4 bytes
+bool igemm_param_reads_nchw(int dtype, int param, int h, int w, int r, int s, int stride, int pad);
 bool igemm_param_valid(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
                        int stride, int pad, int k);
 // whether the tile configuration takes a projected shortcut of c2 channels
@@ -161,6 +164,8 @@ void conv_patch(int dtype, const PatchCfg& cfg, const ConvArgs& a, hipStream_t s
 // conv_smallc.hip); gmax: filter chunks the kernel holds (28 for 7 x 7, 8 for 3 x 3)
 bool smallc_applicable(int layout, int c, int h, int w, int r, int s, int stride, int pad, int n,
                        int k, int fmt, int ppx, int gmax);
+// whether it can read the same input from NCHW planes (4-byte aligned)
+bool smallc_reads_nchw(int h, int w, int r, int s, int stride, int pad, int fmt, int ppx, int gmax);
 // wm: wave rows (of 4 waves); occ: workgroups per CU the persistent grid and
 // the register budget are sized for
 void conv_smallc(int dtype, int fmt, int gmax, const ConvArgs& a, hipStream_t st, int wm = 2, int occ = 3);

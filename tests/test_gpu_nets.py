@@ -514,3 +514,41 @@ def test_addition_in_its_convolutions_launch(dtype, case):
     if dtype != "f32" and r == 3 and k % 8 == 0 and c == 64:
         assert {p for p in fused if p < 106}                     # patch tiles too
     g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("case", [  # (N, C, H, W, K, R, stride, pad)
+    (2, 3, 40, 46, 64, 7, 2, 3), (1, 3, 225, 224, 24, 7, 2, 3), (3, 4, 17, 22, 24, 3, 2, 1), (2, 2, 9, 16, 72, 3, 1, 1),
+    (2, 3, 21, 18, 8, 5, 2, 2), (1, 3, 12, 14, 16, 3, 1, 0), (5, 3, 1, 2, 8, 3, 1, 1), (2, 3, 8, 9, 8, 3, 1, 1)])
+def test_images_read_from_nchw_by_the_small_channel_kernel(dtype, case):
+    """The small-channel kernel reads the caller's planes itself (even widths):
+    the bits of the plan that converts them first, with one launch less; on
+    images that are only 2-byte aligned the converter runs."""
+    import torch
+    from paper_2110_06037_amd import Graph
+    from workloads import random_tensor
+    n, c, h, w, k, r, st, pad = case
+    x = random_tensor((n, c, h, w), dtype, seed=71)
+    wt = random_tensor((k, c, r, r), dtype, seed=72, dist="normal", scale=np.sqrt(2 / (c * r * r)))
+    b = random_tensor((k,), "f32", seed=73, scale=0.1)
+    xd = to_dev(x, dtype)
+    off = torch.empty(xd.numel() + 1, dtype=xd.dtype, device="cuda")[1:].view(xd.shape).copy_(xd)
+    outs, launches = [], []
+    for keep in (1, 0):
+        g = Graph(dtype, n, c, h, w, device=0, layouts=["NCHW", "NHWC"], algos=["igemm"])
+        g.set_option(N.OPT_KEEP, keep)
+        g.add_conv(0, wt, b, st, pad, act="relu")
+        g.add_maxpool(1, 2, 2, 0) if min(h, w) > 4 else g.add_add(1, 1)
+        second = [q["id"] for q in g.routines(2) if q["layout"] == 1][0]
+        ids = [q["id"] for q in g.routines(1) if q["layout"] == 1]
+        assert ids
+        for rid in ids:
+            g.set_path([0, rid, second])
+            outs.append([g.run(t).cpu() for t in (xd, off)])
+            launches.append(len(g.plan_launches()))
+        g.close()
+    m = len(ids)
+    for a, z in zip(outs[:m], outs[m:]):
+        assert all(torch.equal(a[0], t) for t in (a[1], z[0], z[1]))
+    fewer = [a - z for a, z in zip(launches[:m], launches[m:])]
+    assert set(fewer) <= {0, 1} and (1 in fewer) == (w % 2 == 0)
