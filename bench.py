@@ -106,6 +106,7 @@ KERNEL_SOURCES = {
     "igemm_dma_kernel": ("igemm.hpp", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
     "igemm_kernel": ("igemm.hpp", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
     "conv3x3_patch_kernel": ("conv_patch.hip", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
+    "conv3x3_patch_wide_kernel": ("conv_patch.hip", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
     "conv_ksplit_kernel": ("conv_ksplit.hip", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
     "conv1x1_stream_kernel": ("conv1x1_stream.hip", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
     "conv_smallc_kernel": ("conv_smallc.hip", "gemm_common.hpp", "kcommon.hpp", "launch.hpp"),
