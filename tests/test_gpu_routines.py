@@ -544,10 +544,11 @@ def test_wave_split_edges(dtype, ci):
 
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("shape", [(1, 1, 1, 1), (2, 9, 3, 5), (1, 17, 8, 8), (3, 67, 15, 17), (1, 66, 16, 16),
-                                   (8, 2048, 4, 4), (9, 1821, 7, 7), (5, 3277, 2, 4)])
+                                   (8, 2048, 4, 4), (9, 1821, 7, 7), (5, 3277, 2, 4), (19, 1739, 7, 7),
+                                   (32, 1024, 15, 17)])
 def test_gap_planes_edges(dtype, shape):
     """Last workgroups of few planes, runs that are no multiple of 16 bytes,
-    pitches that meet in one bank, both lane counts (from 16384 planes: 4 per
+    pitches that meet in one bank, both lane counts (from 32768 planes: 4 per
     plane), the largest plane; on a tensor that is not 16-byte aligned too."""
     import torch
     x = random_tensor(shape, dtype, seed=17)
