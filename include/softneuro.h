@@ -396,10 +396,13 @@ int sn_integrated_candidate(const sn_graph* g, int32_t idx, int32_t* routine_ids
  * times the selected one's (the max_alts fastest of them) are each run
  * inside the whole path with only that layer's routine swapped (adapts are
  * unchanged: the schema is the same), on a zero-filled scratch input; the
- * layer's time is read from HIP events tied to its first and last launch,
- * the median over reps runs after two warm-up runs.  The fastest routine,
+ * layer's time is read from HIP events tied to its first and last launch of
+ * an sn_run, the median over reps runs after two warm-up runs; where one of
+ * the routines computes the following addition in its launch, the addition's
+ * time counts with it for all of them.  The fastest routine,
  * when it beats the selected one by more than 2 % and does so again in a
- * second pair of timings, replaces it for the later layers' trials.  Finally the selected and the refined path are timed end to end
+ * second pair of timings, replaces it for the later layers' trials.  Finally
+ * the selected and the refined path are timed end to end
  * (four alternating rounds of 20 runs, block means, the median of each) and
  * the faster is kept; its plan is compiled, as after sn_select_path.
  * *n_changed (may be NULL) receives the number of layers whose routine

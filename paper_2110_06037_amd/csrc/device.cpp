@@ -1002,6 +1002,37 @@ static void enqueue_timed(const Graph& g, const Plan& P, const void* const* d_in
   HIPCHK(hipGetLastError());
 }
 
+// One run (the launches of P.fused), in which the steps accounted to the
+// layers of `unit` are timed, in ms: events tied to the first and the last
+// launch of every span of consecutive such steps, the spans added up.
+static float run_unit_ms(const Graph& g, const Plan& P, const std::vector<char>& unit, const void* const* d_in,
+                         void* const* d_out, hipStream_t st, void* flush) {
+  struct Clear {
+    ~Clear() { k::g_timing = k::LaunchTiming{}; }
+  } clear_on_exit;
+  size_t spans = 0;
+  auto in_unit = [&](size_t i) { return i < P.fused.size() && unit[P.fused[i].layer]; };
+  for (size_t i = 0; i < P.fused.size(); ++i) {
+    const bool mine = in_unit(i), first = mine && (i == 0 || !in_unit(i - 1)), last = mine && !in_unit(i + 1);
+    k::g_timing = k::LaunchTiming{};
+    if (first && flush) k::fill_random(SN_F32, flush, g.opt_flush / 4, (uint64_t)i, st);
+    // a layer's steps are consecutive, so there are no more spans than layers
+    k::g_timing = k::LaunchTiming{first ? P.ev[2 * spans] : nullptr, last ? P.ev[2 * spans + 1] : nullptr};
+    enqueue_step(g, P, static_cast<char*>(P.arena), P.fused[i], d_in, d_out, st);
+    if (last) ++spans;
+  }
+  k::g_timing = k::LaunchTiming{};
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(st));
+  float sum = 0.f;
+  for (size_t q = 0; q < spans; ++q) {
+    float ms = 0.f;
+    HIPCHK(hipEventElapsedTime(&ms, P.ev[2 * q], P.ev[2 * q + 1]));
+    sum += ms;
+  }
+  return sum;
+}
+
 void plan_run(Graph& g, const void* const* d_in, void* const* d_out, void* stream, float* layer_ms, int reps) {
   if (!g.plan) fail(SN_E_STATE, "no execution plan");
   HIPCHK(hipSetDevice(g.device));
@@ -1226,9 +1257,11 @@ void integrated_measure(Graph& g, std::vector<Candidate>& cands, int warmup, int
 
 // ------------------------------------------------------------------ in-path refinement
 // Layer by layer, the selected routine and its near-tied alternatives of the
-// same schema are timed inside the whole path (only that layer swapped; the
-// layer's time from the events tied to its first and last launch, median of
-// reps timed runs); a clear winner (more than 2 % faster, confirmed by a second
+// same schema are timed inside the whole path (only that layer swapped, the
+// median of reps runs); what is timed are the launches that a run makes for
+// the layer and for an addition that may run in its launch (a routine that
+// computes the addition competes with one that leaves it to a launch of its
+// own).  A clear winner (more than 2 % faster, confirmed by a second
 // pair of timings) is kept for the later layers' trials.  The refined path then
 // has to beat the selected one end to end (alternating rounds) to be kept.
 int refine_in_path(Graph& g, int tol_permille, int max_alts, int reps, void* stream) {
@@ -1242,15 +1275,22 @@ int refine_in_path(Graph& g, int tol_permille, int max_alts, int reps, void* str
   int changed = 0;
   try {
     ScratchIO io(g, st);
-    std::vector<float> ms(nl);
+    struct Flush {
+      void* p = nullptr;
+      ~Flush() {
+        if (p) (void)hipFree(p);
+      }
+    } flush;
+    if (g.opt_flush > 0) HIPCHK(hipMalloc(&flush.p, (size_t)g.opt_flush));
     std::vector<float> v(reps);
-    auto layer_time = [&](const std::vector<int>& path, int layer) {
+    std::vector<char> unit(nl);
+    const std::vector<int> outs = net_outputs(g);
+    auto layer_time = [&](const std::vector<int>& path) {
       g.path = path;
       plan_compile(g);
-      for (int w = 0; w < 2; ++w) plan_run(g, io.din.data(), io.dout.data(), st, ms.data(), 1);
-      for (int r = 0; r < reps; ++r) {
-        plan_run(g, io.din.data(), io.dout.data(), st, ms.data(), 1);
-        v[r] = ms[layer];
+      for (int r = -2; r < reps; ++r) {
+        const float t = run_unit_ms(g, *g.plan, unit, io.din.data(), io.dout.data(), st, flush.p);
+        if (r >= 0) v[r] = t;
       }
       std::nth_element(v.begin(), v.begin() + reps / 2, v.end());
       return v[reps / 2];
@@ -1269,13 +1309,23 @@ int refine_in_path(Graph& g, int tol_permille, int max_alts, int reps, void* str
       if (alts.empty()) continue;
       std::stable_sort(alts.begin(), alts.end(), [&](int a, int b) { return L.cost[a] < L.cost[b]; });
       if ((int)alts.size() > max_alts) alts.resize(max_alts);
-      const float t0 = layer_time(cur, i);
+      std::fill(unit.begin(), unit.end(), 0);
+      unit[i] = 1;
+      alts.push_back(r0);
+      for (int r : alts) {  // an addition that runs in the launch of one of them
+        g.path = cur;
+        g.path[i] = r;
+        for (int a = 1; a < nl && !g.opt_keep; ++a)
+          if (fusable_conv(g, a, outs) == i) unit[a] = 1;
+      }
+      alts.pop_back();
+      const float t0 = layer_time(cur);
       float best_t = t0;
       int best = r0;
       for (int r : alts) {
         std::vector<int> p = cur;
         p[i] = r;
-        const float t = layer_time(p, i);
+        const float t = layer_time(p);
         if (t < best_t) best_t = t, best = r;
       }
       if (best == r0 || best_t >= 0.98f * t0) continue;
@@ -1283,8 +1333,8 @@ int refine_in_path(Graph& g, int tol_permille, int max_alts, int reps, void* str
       // alternatives the fastest of a noisy set is biased low
       std::vector<int> p = cur;
       p[i] = best;
-      const float t0b = layer_time(cur, i);
-      const float t1b = layer_time(p, i);
+      const float t0b = layer_time(cur);
+      const float t1b = layer_time(p);
       if (t1b < 0.98f * t0b) cur[i] = best;
     }
     for (int i = 0; i < nl; ++i) changed += cur[i] != saved[i];

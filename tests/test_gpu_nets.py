@@ -136,6 +136,48 @@ def test_in_path_refinement_keeps_schemas_and_parity():
     g.close()
 
 
+def test_in_path_refinement_times_the_launches_of_a_run():
+    # a routine that computes the addition after its convolution against one
+    # that is faster on the convolution alone, by less than an addition's
+    # launch takes: swapping it in would add that launch to every run.  The
+    # slow first layer gives the refined path a clear gain in either case, so
+    # the end-to-end comparison does not undo the second layer's swap
+    from paper_2110_06037_amd import Graph
+    rng = np.random.default_rng(5)
+    g = Graph("bf16", 8, 256, 14, 14, device=0, layouts=["NCHW", "NHWC"], algos=["direct", "igemm"])
+    zero = np.zeros(256, np.float32)
+    a = g.add_conv(0, materialise(rng.standard_normal((256, 256, 1, 1)) / 16, "bf16"), zero, act="relu")
+    b = g.add_conv(a, materialise(rng.standard_normal((256, 256, 3, 3)) / 48, "bf16"), zero, pad=1)
+    s = g.add_add(b, a, "relu")
+    g.profile(warmup=5, reps=20)
+    costs = g.costs()
+    nhwc = {i: {r["rid"]: r["ns"] for r in costs["layers"][i]["routines"] if r["layout"] == N.NHWC}
+            for i in (a, b, s)}
+    add = next(iter(nhwc[s]))
+    slow, fast = max(nhwc[a], key=nhwc[a].get), min(nhwc[a], key=nhwc[a].get)
+    fused = set()
+    for r in nhwc[b]:
+        g.set_path([0, fast, r, add])
+        if b not in g.plan_launches():
+            fused.add(r)
+    pairs = [(abs(nhwc[b][f] - nhwc[b][o] - 1300), f, o) for f in fused for o in nhwc[b]
+             if o not in fused and nhwc[b][o] <= 0.9 * nhwc[b][f] and nhwc[b][f] <= nhwc[b][o] + 1600]
+    assert pairs, "no pair of routines a little apart"
+    _, f, o = min(pairs)
+    print("with the addition", nhwc[b][f], "ns, without", nhwc[b][o], "ns; first layer", nhwc[a][slow], nhwc[a][fast])
+    for l in costs["layers"][1:-1]:                # only these routines, as near ties
+        for r in l["routines"]:
+            r["ns"] = 10000 if (l["id"], r["rid"]) in {(a, slow), (a, fast), (b, f), (b, o), (s, add)} else -1
+            r.pop("child", None)
+    g.set_costs(costs)
+    g.set_path([0, slow, f, add])
+    launches = len(g.plan_launches())
+    n = g.refine_in_path(tol_permille=100, max_alts=3, reps=15)
+    assert g.path()[0] == [0, fast, f, add] and n == 1
+    assert len(g.plan_launches()) <= launches
+    g.close()
+
+
 @pytest.mark.parametrize("name", ["resnet18", "mobilenetv2", "resnet50_bf16", "resnet50_f16",
                                   "resnet50_fused", "resnet50_proj", "mobilenetv2_fused", "vgg16_64px"])
 def test_net_dp_and_fixed_paths_match_oracle(name):
