@@ -215,10 +215,17 @@ void dev_upload_layer(Graph& g, int id) {
   dl.bias = static_cast<float*>(dev_upload(bias.data(), bias.size() * 4));
   const uint8_t* src = L.weight.data();
   const int R = L.d.r, S = L.d.s;
-  // the order of the wave-split kernel: routine parameters of the 16-bit
-  // types, part of fp32's one implicit-GEMM routine
+  // the order of the wave-split kernel, a second copy of the filter: for the
+  // dtypes in which a routine of the layer runs on that kernel
+  bool ks[3] = {};
+  const bool fc = L.type == SN_LAYER_FC;
+  for (const Routine& r : L.routines)
+    if (r.algo == SN_ALGO_IGEMM && !is_depthwise(g, L))
+      ks[r.dtype] |= k::igemm_param_is_ksplit(r.dtype, r.param, r.layout, in.n, C, in.h, in.w, fc ? 1 : R, fc ? 1 : S,
+                                              fc ? 1 : L.d.stride, fc ? 0 : L.d.pad, K,
+                                              L.proj_stride > 0 ? g.layers[L.inputs[1]].out.c : 0);
   auto upload_ks = [&](const std::vector<uint8_t>& w, int dt) -> void* {
-    if (!(g.opt_algos >> SN_ALGO_IGEMM & 1) || (!g.opt_params && dt != SN_F32)) return nullptr;
+    if (!ks[dt]) return nullptr;
     const size_t row = w.size() / Kp, bytes = k::ksplit_packed_bytes(Kp, row);
     if (bytes >= size_t(1) << 31) return nullptr;  // beyond the kernel's offsets
     std::vector<uint8_t> o(bytes);

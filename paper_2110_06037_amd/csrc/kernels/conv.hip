@@ -65,6 +65,12 @@ bool igemm_param_takes_residual(int dtype, int param, int layout, int k) {
   return g.dma == 0 || g.dma == 5 || (g.dma == 1 && (layout == NC8 || k % 8 == 0)) || (g.dma == 4 && layout == NHWC && k % 8 == 0);
 }
 
+bool igemm_param_is_ksplit(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s, int stride,
+                           int pad, int k, int c2) {
+  if (dtype == 0) return ksplit_tile_f32(layout, n, c, h, w, r, s, stride, pad, k, c2) != 0;
+  return kIg16[param].dma == 5;
+}
+
 // fp32 has nothing to round; in 16-bit types the wave-split and the 3x3 patch
 // kernel (16-byte stores)
 bool igemm_param_fuses_add(int dtype, int param, int layout, int k) {

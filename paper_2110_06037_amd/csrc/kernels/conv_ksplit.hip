@@ -339,7 +339,7 @@ void ksplit_pack(const void* w, int kp, size_t row_bytes, void* out) {
 // wave-split step has four times the loads, 1.65 of its NHWC time.  LDS tile ->
 // pick: 16 channels 3x3/2 at 32 x 32, 10.3 -> 5.1 us; 64 at 2 x 28 x 28, 28.0 -> 9.2; 512
 // at 7 x 7, 188 -> 14.9; 256 at 8 x 14 x 14, 98 -> 39.
-int ksplit_pick_f32(int layout, long long m, int k, long long red, bool lds_ok) {
+static int ksplit_pick_f32(int layout, long long m, int k, long long red, bool lds_ok) {
   struct Fit {
     int fm, fn;
     double step, tile;
@@ -377,6 +377,12 @@ bool ksplit_applicable(int dtype, int layout, int n, int c, int h, int w, int r,
          n * c8 * h * w * es < (long long)kOOB &&
          ksplit_packed_bytes((int)kp, (size_t)(r * s * c8 * es)) < kOOB && n * kp * p * q * es < (long long)kOOB &&
          ksplit_packed_bytes((int)kp, (size_t)(k2 * es)) < kOOB;
+}
+
+int ksplit_tile_f32(int layout, int n, int c, int h, int w, int r, int s, int stride, int pad, int k, int c2) {
+  if (!ksplit_applicable(0, layout, n, c, h, w, r, s, stride, pad, k, c2)) return 0;
+  const long long p = (h + 2 * pad - r) / stride + 1, q = (w + 2 * pad - s) / stride + 1;
+  return ksplit_pick_f32(layout, n * p * q, k, (long long)r * s * (layout == NCHW ? (c + 7) / 8 * 8 : c) + c2, !c2);
 }
 
 template <typename T, int L, int FM, int FN, int NW, int D>

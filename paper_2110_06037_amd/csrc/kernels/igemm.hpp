@@ -1383,16 +1383,13 @@ static void igemm_dispatch(int dtype, int param, const ConvArgs& c, hipStream_t 
   }
   if constexpr (std::is_same<T, float>::value) {
     // fp32 has one parameter; the tile follows from the size
-    if (c.wks && ksplit_applicable(dtype, c.xd.layout, c.xd.n, c.xd.c, c.xd.h, c.xd.w, c.r, c.s, c.stride, c.pad,
-                                   c.yd.c, c.x2 ? c.x2d.c : 0)) {
-      const int cc = c.xd.layout == NCHW ? (c.xd.c + 7) / 8 * 8 : c.xd.c;
-      const int t = ksplit_pick_f32(c.xd.layout, (long long)c.yd.n * c.yd.h * c.yd.w, c.yd.c,
-                                    (long long)c.r * c.s * cc + (c.x2 ? c.x2d.c : 0), !c.x2);
-      if (t) {
-        check(!c.res || !c.x2, "a projected shortcut replaces the residual");
-        conv_ksplit(dtype, t / 8, t % 8, 8, c, st);
-        return;
-      }
+    const int t = c.wks ? ksplit_tile_f32(c.xd.layout, c.xd.n, c.xd.c, c.xd.h, c.xd.w, c.r, c.s, c.stride, c.pad,
+                                          c.yd.c, c.x2 ? c.x2d.c : 0)
+                        : 0;
+    if (t) {
+      check(!c.res || !c.x2, "a projected shortcut replaces the residual");
+      conv_ksplit(dtype, t / 8, t % 8, 8, c, st);
+      return;
     }
   }
   check(!c.round_sum || (c.res && igemm_param_fuses_add(dtype, param, c.yd.layout, c.yd.c)),

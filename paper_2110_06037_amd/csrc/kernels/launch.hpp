@@ -99,6 +99,10 @@ bool igemm_param_fuses_add(int dtype, int param, int layout, int k);
 bool igemm_param_reads_nchw(int dtype, int param, int h, int w, int r, int s, int stride, int pad);
 bool igemm_param_valid(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
                        int stride, int pad, int k);
+// whether the parameter, offered for the layer, runs it on the wave-split
+// kernel (c2: as below, 0 without a projected shortcut)
+bool igemm_param_is_ksplit(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s, int stride,
+                           int pad, int k, int c2);
 // whether the tile configuration takes a projected shortcut of c2 channels
 // (besides being valid for the convolution itself)
 bool igemm_param_takes_projection(int dtype, int param, int layout, int n, int c, int h, int w, int r, int s,
@@ -226,10 +230,9 @@ void conv1x1_stream(int dtype, int cc, int bm, int bn, int pd, const ConvArgs& a
   X(4, 4, 8, 2)
 bool ksplit_applicable(int dtype, int layout, int n, int c, int h, int w, int r, int s, int stride, int pad, int k,
                        int c2);
-// the fp32 implicit GEMM's tile in the layout for m output pixels, k output channels and
-// a reduction of red (NCHW: over the channels rounded up to 8): FM * 8 + FN of a wave-split tile, or 0 for the LDS
-// tile (lds_ok: whether that one can run the layer)
-int ksplit_pick_f32(int layout, long long m, int k, long long red, bool lds_ok);
+// the fp32 implicit GEMM's tile for a layer (c2 as above): FM * 8 + FN of a
+// wave-split tile, or 0 for the LDS tile
+int ksplit_tile_f32(int layout, int n, int c, int h, int w, int r, int s, int stride, int pad, int k, int c2);
 // the kernel's filter order: kp rows of row_bytes (a multiple of 16) as blocks
 // of 16 rows x 4 chunks of 16 bytes, each 1 KB in lane order
 size_t ksplit_packed_bytes(int kp, size_t row_bytes);

@@ -542,6 +542,23 @@ def test_wave_split_edges(dtype, ci):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,hw,copies", [("bf16", 96, 1), ("bf16", 7, 2), ("f32", 96, 1), ("f32", 7, 2)])
+def test_wave_split_filter_copy_only_where_a_routine_reads_it(dtype, hw, copies):
+    # a 1024-channel 3x3 filter (18 MiB in 16 bits, 36 in fp32) is held a
+    # second time, in the wave-split kernel's order, only if the layer has a
+    # routine that runs on that kernel: not at 96 x 96 (2304 workgroups of its
+    # largest 16-bit tile, and in fp32 the LDS tile is the faster one)
+    import torch
+    w = np.zeros((1024, 1024, 3, 3), np.uint16 if dtype == "bf16" else np.float32)
+    g = Graph(dtype, 1, 1024, hw, hw, device=0, layouts=["NHWC"], algos=["igemm"])
+    before = torch.cuda.mem_get_info()[0]
+    g.add_conv(0, w, np.zeros(1024, np.float32), pad=1)
+    held = before - torch.cuda.mem_get_info()[0]
+    size = w.nbytes
+    assert abs(held - copies * size) < size // 4
+    g.close()
+
+
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("shape", [(1, 1, 1, 1), (2, 9, 3, 5), (1, 17, 8, 8), (3, 67, 15, 17), (1, 66, 16, 16),
                                    (8, 2048, 4, 4), (9, 1821, 7, 7), (5, 3277, 2, 4), (19, 1739, 7, 7),
