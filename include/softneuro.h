@@ -159,6 +159,10 @@ typedef enum {
                            that memory restriction (the restriction Sec. VI names
                            as future work; Winograd's transforms are its example).
                            -1 = no limit (the default); 0 = no workspace at all.
+                           With a limit the plan's intermediate tensors are also
+                           packed as tightly as their lifetimes allow; without one
+                           the plan may use up to 150 MiB to leave a dead tensor's
+                           bytes unused for some steps (or all), which is faster.
                            A layer left with no routine is refused by
                            sn_add_layer (SN_E_UNSUPPORTED).  A routine-set option:
                            set it before adding layers                               */

@@ -938,16 +938,32 @@ void plan_compile(Graph& g) {
   // 512 x 28 x 28 bottlenecks at batch 8 86.5 (0), 84.4 (1), 81.4 (4), 80.2 (no reuse).  A
   // plan past 150 MiB without rest streams anyway and is packed as tightly as before:
   // ResNet-50 batch 64 1089 (0: 220 MiB), 1109 (1).
-  const size_t spread = size_t(150) << 20;
-  static const int holds[] = {INT32_MAX, 8, 4, 2, 1};
-  for (int hold : holds) {
-    std::unique_ptr<Plan> Q = plan_layout(g, true, true, hold);
-    if (Q->arena_bytes > spread) continue;
-    P = std::move(Q);
-    break;
+  // Under a memory restriction (SN_OPT_WS_LIMIT) nothing rests, and of the
+  // layouts with and without shared copies and fused additions the smaller is
+  // taken: the peak is that of the live tensors and one step's workspace.
+  if (g.opt_ws_limit >= 0) {
+    std::unique_ptr<Plan> Q = plan_layout(g, false, false, 0);
+    if (Q->arena_bytes < P->arena_bytes) P = std::move(Q);
+  } else {
+    const size_t spread = size_t(150) << 20;
+    static const int holds[] = {INT32_MAX, 8, 4, 2, 1};
+    for (int hold : holds) {
+      std::unique_ptr<Plan> Q = plan_layout(g, true, true, hold);
+      if (Q->arena_bytes > spread) continue;
+      P = std::move(Q);
+      break;
+    }
+  }
+  // a device with less free memory than that still gets the packed layouts
+  for (int packed = 0;; ++packed) {
+    const hipError_t e = hipMalloc(&P->arena, P->arena_bytes);
+    if (e == hipSuccess) break;
+    (void)hipGetLastError();
+    if (e != hipErrorOutOfMemory || packed == 2)
+      fail(SN_E_DEVICE, "arena of " + std::to_string(P->arena_bytes) + " bytes: " + hipGetErrorString(e));
+    P = plan_layout(g, packed == 0, packed == 0, 0);
   }
   if (P->arena_bytes > region) P->tight = std::move(tight);
-  HIPCHK(hipMalloc(&P->arena, P->arena_bytes));
   P->ev.resize(2 * n, nullptr);
   for (auto& e : P->ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
   g.plan = std::move(P);

@@ -232,6 +232,28 @@ def test_workspace_limited_selection_runs_within_the_limit():
     g.close()
 
 
+@pytest.mark.parametrize("ws_limit", [0, None])
+def test_workspace_limit_packs_the_intermediate_tensors(ws_limit):
+    # six 12.8 MB maps in a chain: under a memory restriction two are alive at
+    # a time; without one each gets bytes of its own (below 150 MiB in all)
+    import torch
+    from paper_2110_06037_amd import Graph
+    rng = np.random.default_rng(3)
+    g = Graph("bf16", 32, 64, 56, 56, device=0, layouts=["NHWC"], algos=["igemm"], ws_limit=ws_limit)
+    last = 0
+    for _ in range(5):
+        last = g.add_conv(last, materialise(rng.standard_normal((64, 64, 1, 1)) / 8, "bf16"), np.zeros(64, np.float32),
+                          act="relu")
+    size = 32 * 64 * 56 * 56 * 2
+    ids = [0] + [next(r["id"] for r in g.routines(i) if r["ws_bytes"] == 0) for i in range(1, last + 1)]
+    before = torch.cuda.mem_get_info()[0]
+    g.set_path(ids)
+    held = before - torch.cuda.mem_get_info()[0]
+    maps = 2 if ws_limit == 0 else 6           # the converted input and five outputs
+    assert abs(held - maps * size) < size // 2
+    g.close()
+
+
 def test_resnet50_bs32_dp_path_sampled_images():
     # the benchmark's configuration: full batch on the GPU, images 0 and 1
     # through the oracle (images are independent)
