@@ -377,6 +377,8 @@ void select_fixed(Graph& g, int layout, int algo, int dtype) {
       int best = -1;
       for (const Routine& r : L.routines) {
         if (r.layout != layout || r.algo != want_algo || r.dtype != dtype) continue;
+        // a cost table without the appended routines selects among the others
+        if (g.have_costs && r.id >= L.n_base && L.cost[r.id] < 0) continue;
         if (best < 0) {
           best = r.id;
           continue;

@@ -461,6 +461,56 @@ def test_workspace_limit_restricts_the_routine_set():
     g.close()
 
 
+@pytest.mark.parametrize("limited", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_cost_tables_from_before_the_appended_routines(dtype, limited):
+    # a table that ends before a layer's appended routines (in 16 bits the
+    # parameters from 106 on, of every layout; in fp32 the implicit GEMM of a
+    # projected shortcut) loads; those routines have no time and no selection
+    # takes them.  Also where a workspace limit (that of the projection's
+    # two launches) took earlier routines away.
+    ar = np.uint16 if dtype == "bf16" else np.float32
+    limit = 2 * 64 * 14 * 14 * ar().nbytes if limited else None
+    g = Graph(dtype, 2, 64, 14, 14, device=-1, ws_limit=limit)
+    b = np.zeros(64, np.float32)
+    c1 = g.add_conv(0, np.zeros((64, 64, 3, 3), ar), b, 1, 1)
+    # 40 shortcut channels: no projection on the LDS-DMA tiles, so in 16 bits,
+    # too, every implicit GEMM of the layer is an appended one
+    c2 = g.add_conv(c1, np.zeros((40, 64, 1, 1), ar), np.zeros(40, np.float32))
+    p = g.add_projected_conv(c1, c2, np.zeros((64, 64, 3, 3), ar), b, np.zeros((64, 40), ar), b, 1, 1)
+    g.add_add(p, c1)
+    full = randomise(g.costs(), 21, max_cost=50)
+    old = json.loads(json.dumps(full))
+    cut = {}
+    for l in old["layers"][1:-1]:
+        def appended(r):
+            return r["algo"] == N.IGEMM and (r["param"] >= 106 if dtype == "bf16" else l["id"] == p)
+        keep = [r for r in l["routines"] if not appended(r)]
+        assert keep == l["routines"][:len(keep)]                  # they come last
+        cut[l["id"]] = len(keep)
+        l["routines"] = keep
+    assert (cut[c1] < len(g.routines(c1))) == (dtype == "bf16") and cut[p] < len(g.routines(p))
+    got = dp_vs(g, old)
+    assert got == exhaustive(problem_from_costs(old))[1::-1]
+    for i, n in cut.items():
+        assert [r["cost_ns"] for r in g.routines(i)][n:] == [-1] * (len(g.routines(i)) - n)
+    for lay in ("NCHW", "NHWC", "NC8HW8"):
+        for algo in ("direct", "igemm"):
+            g.select("fixed", lay, algo)
+            ids, total = g.path()
+            assert total >= 0 and all(ids[i] < n for i, n in cut.items()), (lay, algo)
+    # one routine less, and a list cut inside the appended ones
+    for i, n in ((c1, cut[c1] - 1), (p, cut[p] + 1)):
+        if n == len(full["layers"][i]["routines"]):
+            continue
+        bad = json.loads(json.dumps(full))
+        bad["layers"][i]["routines"] = bad["layers"][i]["routines"][:n]
+        assert status_of(g.set_costs, bad) == -1
+    g.set_costs(full)
+    assert all(r["cost_ns"] >= 0 for r in g.routines(p))
+    g.close()
+
+
 def test_childnet_routine_time_is_the_optimum_over_its_sub_layers():
     # The three-kernel Winograd routines are childnets (Sec. III-D): wgenc ->
     # wgconv (one sub-routine per GEMM tile) -> wgdec.  Its time in the cost
