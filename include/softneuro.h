@@ -147,8 +147,9 @@ typedef enum {
                            before each timed run (cache-cold unit profiling);
                            0 = off, the default                                     */
   SN_OPT_KEEP = 6,      /* 1: the plan gives every intermediate tensor its own bytes
-                           (no reuse by liveness), so sn_layer_output can read any
-                           layer's stored output after a run (default 0)            */
+                           (no reuse by liveness) and every layer launches of its
+                           own, so sn_layer_output can read any layer's stored
+                           output after a run (default 0)                           */
   SN_OPT_DTYPES = 7,    /* bitmask of element types routines may compute in (bit =
                            sn_dtype), default the run dtype only; with more than one
                            every layer gets routines in each, and adapts cast
@@ -210,8 +211,9 @@ int sn_add_layer(sn_graph* g, const sn_layer_desc* d, const int32_t* inputs, int
  * into the convolution that produces the add's other operand (layer fusion,
  * Sec. III-A): one layer of two inputs whose routines compute both products
  * in one reduction (implicit GEMM on the LDS-DMA tiles, 16-bit channel-vector
- * layouts with C and C2 multiples of the tile depth) or, in any layout and
- * dtype, as the projection followed by the convolution with a residual
+ * layouts with C and C2 multiples of the tile depth; on the wave-split kernel,
+ * every dtype, NHWC with C and C2 multiples of 8 or NC8HW8) or, in any layout
+ * and dtype, as the projection followed by the convolution with a residual
  * (direct routine, two launches and a workspace).  weight: OIHW [K][C][R][S],
  * shortcut_weight [K][C2] in the run dtype, host memory, copied; biases
  * float32 [K] or NULL = zeros (the two are summed in float64 and rounded
@@ -295,24 +297,31 @@ int sn_run_mimo(sn_graph* g, const void* const* d_ins, int32_t n_in, void* const
 
 /* sn_run without allocation, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * it).  The same launches as sn_run on the same selected plan, with the
- * plan's intermediate tensors and workspaces (split-reduction partial sums,
- * Winograd transforms) placed in the library's static per-device region of
- * 64 MiB instead of the plan's own memory; the call itself allocates nothing
- * and enqueues nothing but kernels (no memset, no copy), so results are
- * identical to sn_run's.  Every call on one GPU shares that GPU's region, and
+ * it).  The routines of the same selected plan, with its intermediate tensors
+ * and workspaces (split-reduction partial sums, Winograd transforms) placed in
+ * the library's static per-device region of 64 MiB instead of the plan's own
+ * memory; the call itself allocates nothing and enqueues nothing but kernels
+ * (no memset, no copy).  The tensors are packed there, and where sn_run's
+ * shared converted copies and additions in a convolution's launch would take
+ * more than the region, every layer runs on its own: more launches than
+ * sn_run's, the same bits in the output.  Every call on one GPU shares that GPU's region, and
  * the region keeps the last call's contents (no routine relies on it being
  * zero): calls that overlap in time on one GPU (different streams, different
  * threads, or different graphs without ordering between them) race and give
  * undefined results.  d_in / d_out as for sn_run.
  * Errors: SN_E_STATE (no plan), SN_E_UNSUPPORTED (the plan needs more than
- * the 64 MiB region, e.g. ResNet-50 at batch 32: use sn_run), SN_E_DEVICE. */
+ * the 64 MiB region also then, e.g. ResNet-50 at batch 32: use sn_run),
+ * SN_E_DEVICE. */
 int sn_run_noalloc(sn_graph* g, const void* d_in, void* d_out, void* hip_stream);
 
 /* Like sn_run, but enqueues every layer's launches (its routine plus the
  * converters feeding it) reps times back to back, then synchronises and
  * writes each layer's mean time per repetition to layer_ms[0..n-1] (layer 0
- * gets 0).  HIP events are tied to the start of a layer's first kernel
+ * gets 0).  Every layer runs on its own: where sn_run computes an addition in
+ * its convolution's launch, or a convolution reads the net's input without
+ * the converter, here they are launches of their own, and their times add up
+ * to more than sn_run takes.  A converted copy that several layers read is
+ * timed with the first of them.  HIP events are tied to the start of a layer's first kernel
  * dispatch and the end of its last (hipExtLaunchKernelGGL), so host launch
  * latency and the events' own dispatch gaps are amortised over reps.  Every
  * launch writes buffers distinct from the ones it reads, so d_out holds the
@@ -344,7 +353,11 @@ int sn_layer_output(const sn_graph* g, int32_t layer, void* d_dst, size_t cap, s
 /* The kernel launches one sn_run of the selected plan makes, in order:
  * layer_of_launch[i] is the layer launch i belongs to (the adapt routines
  * feeding a layer count as that layer's; a routine may launch more than one
- * kernel).  Nothing is launched: the plan's steps are walked with launches
+ * kernel).  A launch that computes a convolution and the addition after it is
+ * the addition's; the convolution then has no launch of its own beyond its
+ * converters.  Listed for input and output tensors aligned to 16 bytes: a
+ * convolution that reads 16-bit images without a converter needs them 4-byte
+ * aligned, and else one more launch converts them.  Nothing is launched: the plan's steps are walked with launches
  * counted only.  Lets a kernel trace of sn_run (for instance per-dispatch
  * hardware counters) be attributed to layers.  *n receives the count;
  * layer_of_launch = NULL only queries it.

@@ -1121,7 +1121,8 @@ void plan_run(Graph& g, const void* const* d_in, void* const* d_out, void* strea
 
 // sn_run with the plan's intermediate tensors and workspaces placed in a
 // caller-provided device region of cap bytes instead of the plan's own
-// memory (same offsets, same launches, hence the same results).  Enqueues
+// memory: the plan's layout, or the tight one beside it (other offsets,
+// perhaps without fused steps and shared copies; the same bits).  Enqueues
 // only kernel launches: no allocation, no memset.
 void plan_run_in(const Graph& g, void* base, size_t cap, const void* const* d_in, void* const* d_out,
                  void* stream) {

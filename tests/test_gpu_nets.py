@@ -527,6 +527,57 @@ def test_adapts_making_one_conversion_share_its_result(hw):
     g.close()
 
 
+def test_noalloc_run_without_the_fused_launches():
+    # 47 images of 3 x 56 x 56 through a stem, two 3x3 layers and an addition,
+    # maps of 18.9 MB: with the addition in its convolution's launch four are
+    # alive at once (72 MiB), layer by layer three (54 MiB), so sn_run_noalloc
+    # runs the layers one by one, the stem behind its converter, to the same bits
+    import torch
+    from paper_2110_06037_amd import Graph
+    rng = np.random.default_rng(9)
+    n, k, hw = 47, 64, 56
+    g = Graph("bf16", n, 3, hw, hw, device=0, layouts=["NHWC"], algos=["igemm"])
+
+    def wts(c):
+        return materialise(rng.standard_normal((k, c, 3, 3)) / np.sqrt(4.5 * c), "bf16")
+    b = rng.uniform(-0.1, 0.1, k).astype(np.float32)
+    ws = [wts(3), wts(k), wts(k)]
+    stem = g.add_conv(0, ws[0], b, pad=1, act="relu")
+    c1 = g.add_conv(stem, ws[1], b, pad=1, act="relu")
+    c2 = g.add_conv(c1, ws[2], b, pad=1)
+    a = g.add_add(c2, stem, "relu")
+
+    def fewest(layer, ids):
+        best = None
+        for r in g.routines(layer):
+            if r["ws_bytes"]:
+                continue
+            g.set_path(ids[:layer] + [r["id"]] + ids[layer + 1:])
+            m = len(g.plan_launches())
+            if best is None or m < best[0]:
+                best = (m, r["id"])
+        return ids[:layer] + [best[1]] + ids[layer + 1:]
+    plain = [next(r["id"] for r in g.routines(i) if r["ws_bytes"] == 0) for i in range(1, a + 1)]
+    ids = fewest(c2, fewest(stem, [0] + plain))
+    g.set_path(ids)
+    # the stem without its converter, the addition in c2's launch, the output's converter
+    assert g.plan_launches() == [stem, c1, a, a]
+    x = materialise(rng.uniform(-1, 1, (n, 3, hw, hw)), "bf16")
+    xd = to_dev(x, "bf16")
+    out = g.run(xd)
+    d = [to_f64(w, "bf16") for w in ws]
+    x1, b64 = to_f64(x[:1], "bf16"), b.astype(np.float64)
+    s0 = O.round_to(O.conv2d(x1, d[0], b64, 1, 1, 1, "relu"), "bf16")
+    h = O.round_to(O.conv2d(s0, d[1], b64, 1, 1, 1, "relu"), "bf16")
+    h = O.round_to(O.conv2d(h, d[2], b64, 1, 1), "bf16")
+    assert err(from_dev(out, "bf16")[:1], O.round_to(O.add(h, s0, "relu"), "bf16"), "bf16") <= TOL["bf16"]
+    out2 = torch.zeros_like(out)
+    g.run_noalloc(xd, out2)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2)
+    g.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 # (C, K, H, W, R, act, addition's operand order): ragged pixel and channel
 # tiles; K % 8 != 0 (element stores); every patch tile applies at 64 channels
