@@ -420,9 +420,9 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
 // LDS: 9 operand reads for 14 MFMAs, 72 KB per tap against the 56 KB that the
 // matrix cores' time admits, since its stage holds all 9 taps' filter rows and
 // leaves room for 64 channels.  Here only one tap row's filter rows (3 taps, 24 KB)
-// are a stage, three of them rotating, beside two patch buffers: 144 KB hold a
-// tile of 128 channels, each wave has 7 x 4 blocks (11 reads for 28 MFMAs),
-// and each input element is read by half as many workgroups.
+// are a stage, three of them rotating, beside two patch buffers: 152 KB (136 at
+// the patch pitch of 32) hold a tile of 128 channels, each wave has 7 x 4
+// blocks (11 reads for 28 MFMAs), and each input element is read by half as many workgroups.
 // Against the fastest other routine in fp16 at batch 32 (a library product of 8192^3
 // reaches 1.15 PFLOP/s here): 256 channels at 56 x 56, 111.4 -> 106.3 us (1.11 PFLOP/s);
 // 512 at 28 x 28, 119.7 -> 100.2 (1.18); 256 -> 512 there, 64.4 -> 52.9.  Below one
@@ -430,7 +430,8 @@ __global__ __launch_bounds__(512, 2 * OCC) void conv3x3_patch_kernel(PatchArgs a
 // others.  Reading the next tap row's first operands before its barrier needs more
 // registers than there are (50 spilled, 188 us).
 // FMT = 28 row blocks, 4 x 2 waves; the tile's row blocks are consecutive LDS
-// rows, so all operand addresses are three registers plus immediates.
+// rows, so all operand addresses are four registers (one for the filter, one
+// per tap column for the patch) plus immediates.
 template <typename T, int L, int FMT, int BN, int PWT, int PROWS>
 __global__ __launch_bounds__(512, 2) void conv3x3_patch_wide_kernel(PatchArgs a) {
   static_assert(sizeof(T) == 2 && L != NCHW, "16-bit channel-vector layouts only");

@@ -221,7 +221,7 @@ void conv1x1_stream(int dtype, int cc, int bm, int bn, int pd, const ConvArgs& a
 // type; NCHW, fp32, without a projected shortcut; c2 > 0: with a projected shortcut of c2 channels).  Instantiated
 // tiles (FM, FN, NW, D): 16 FM pixels x 16 FN channels, NW waves, D reduction
 // steps in flight per wave; in 16-bit types each is one implicit-GEMM routine
-// parameter, in fp32 the one routine takes a tile by size (ksplit_pick_f32).
+// parameter, in fp32 the one routine takes a tile by size (ksplit_tile_f32).
 #define KSPLIT_CONFIGS(X) \
   X(1, 1, 8, 6)           \
   X(2, 1, 8, 4)           \
