@@ -932,12 +932,18 @@ void plan_compile(Graph& g) {
   // Bytes that a kernel has just read or written are slow to overwrite (their
   // lines sit in other XCDs' caches), so a dead buffer's bytes rest for as
   // many steps as the arena stays within 150 MiB, which the 256 MB Infinity
-  // Cache holds beside weights and caller's tensors.  us per run by steps of rest:
-  // ResNet-50 batch 32 641 (0: 110 MiB), 627 (1), 626 (2: 147 MiB), 681 (4: 208),
-  // 722 (no reuse: 608); batch 8 426 (0), 411 (1), 397 (4 to no reuse: 157 MiB);
-  // 512 x 28 x 28 bottlenecks at batch 8 86.5 (0), 84.4 (1), 81.4 (4), 80.2 (no reuse).  A
-  // plan past 150 MiB without rest streams anyway and is packed as tightly as before:
-  // ResNet-50 batch 64 1089 (0: 220 MiB), 1109 (1).
+  // Cache holds beside weights and caller's tensors.  us per run by steps of rest
+  // (MiB), median of six rounds in turn, bf16:
+  // ResNet-50 batch 8  424 (0: 28), 411 (1: 34), 398 (4: 52), 397 (8: 66), 403 (no reuse: 156)
+  //           batch 32 687 (0: 110), 673 (1: 135), 675 (2: 147), 704 (3: 184), 728 (4: 208), 763 (608)
+  //           batch 40 819 (0: 138), 812 (1: 168), 819 (2: 184), 871 (3: 230)
+  //           batch 48 947 (0: 165), 981 (1: 202); batch 64 1163 (0: 220), 1163 (1: 270)
+  // ResNet-18 batch 64 478 (0: 123), 467 (1: 147), 467 (2: 172), 469 (3: 196), 483 (4: 221)
+  // MobileNetV2 batch 32 480 (0: 92), 480 (1: 110), 440 (2: 153), 428 (4: 168), 452 (8: 245)
+  // VGG16 batch 8 479 (0: 98), 469 (1: 110), 472 (2: 135); batch 16 818 (0: 196), 812 (1: 221)
+  // So rest pays up to about 150 MiB everywhere; from there to 200 it depends on
+  // the net, and past 200 it costs where it does anything.  A plan past 150 MiB
+  // without rest streams anyway and is packed as tightly as before.
   // Under a memory restriction (SN_OPT_WS_LIMIT) nothing rests, and of the
   // layouts with and without shared copies and fused additions the smaller is
   // taken: the peak is that of the live tensors and one step's workspace.
