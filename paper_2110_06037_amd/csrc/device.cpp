@@ -942,7 +942,7 @@ void plan_compile(Graph& g) {
   // MobileNetV2 batch 32 480 (0: 92), 480 (1: 110), 440 (2: 153), 428 (4: 168), 452 (8: 245)
   // VGG16 batch 8 479 (0: 98), 469 (1: 110), 472 (2: 135); batch 16 818 (0: 196), 812 (1: 221)
   // So rest pays up to about 150 MiB everywhere; from there to 200 it depends on
-  // the net, and past 200 it costs where it does anything.  A plan past 150 MiB
+  // the net, and past 200 it mostly costs.  A plan past 150 MiB
   // without rest streams anyway and is packed as tightly as before.
   // Under a memory restriction (SN_OPT_WS_LIMIT) nothing rests, and of the
   // layouts with and without shared copies and fused additions the smaller is
