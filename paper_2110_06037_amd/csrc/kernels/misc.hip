@@ -209,12 +209,14 @@ __global__ __launch_bounds__(256) void gap_kernel(const T* __restrict__ x, T* __
 // net): a wave per plane had one 2- or 4-byte load per lane in flight and most of
 // its time went to launching 16384 workgroups of four planes.  A
 // workgroup takes 256 / TPP consecutive planes, which are one run of memory: 16-byte
-// loads bring it to LDS, then TPP lanes sum a plane.  Each plane's sum starts at a
+// loads bring it to LDS, then TPP lanes sum a plane, in 64 partial sums per plane as
+// the wave does (in fp32, four sums of up to 64 pixels one after the other were
+// 1.6 times as far from the exact mean on centred planes of 15 x 17).  Each plane's sum starts at a
 // pixel of its own: planes of 64 or 128 pixels would otherwise meet in one bank.
 // The run starts 16-byte aligned with x (256 / TPP planes are a multiple of 8).
-// bf16, block means, wave per plane -> this: 32 x 2048 planes of 7 x 7, 6.3 -> 3.8 us
-// (1.7 TB/s); of 12 x 12,
-// 8.2 -> 5.7; 8 x 1280 of 7 x 7, 3.5 -> 2.5.
+// bf16, block means, wave per plane -> one sum per lane -> this: 32 x 2048 planes of
+// 7 x 7, 6.3 -> 3.8 -> 3.3 us (1.9 TB/s); 32 x 1024 of 12 x 12, 4.9 -> 4.25 from the
+// second; 8 x 1280 of 7 x 7, 3.5 -> 2.7.
 template <typename T, int TPP>
 __global__ __launch_bounds__(256) void gap_planes_kernel(const T* __restrict__ x, T* __restrict__ y,
                                                          long long planes, int HW) {
@@ -234,15 +236,28 @@ __global__ __launch_bounds__(256) void gap_planes_kernel(const T* __restrict__ x
   }
   __syncthreads();
   const int pl = threadIdx.x / TPP, j = threadIdx.x % TPP;
-  float s = 0.f;
-  if (pl < np) {
-    int i = (j + 2 * pl) % HW;  // pixels j, j + TPP, ... counted from 2 pl
-    for (int n = j; n < HW; n += TPP) {
-      s += to_f(run[pl * HW + i]);
-      i += TPP;
-      if (i >= HW) i %= HW;
+  constexpr int NA = 64 / TPP;
+  float acc[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) acc[a] = 0.f;
+  int i = (j + 2 * pl) % HW;  // pixels j, j + TPP, ... counted from 2 pl
+  const int step = TPP % HW;
+  // (the lanes of planes past np read what lies in the LDS and store nothing)
+  for (int n = 0; n < HW; n += 64) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      if (n + a * TPP >= HW) break;  // the same for every lane
+      const float v = to_f(run[pl * HW + i]);
+      acc[a] += n + a * TPP + j < HW ? v : 0.f;
+      i += step;
+      if (i >= HW) i -= HW;
     }
   }
+#pragma unroll
+  for (int h = NA / 2; h > 0; h /= 2)
+#pragma unroll
+    for (int a = 0; a < h; ++a) acc[a] += acc[a + h];
+  float s = acc[0];
   s += dpp_take<0xB1>(s);  // within a quad: XOR 1, XOR 2
   s += dpp_take<0x4E>(s);
   if constexpr (TPP > 4) s += dpp_take<0x141>(s);  // the half-row's other quad
@@ -263,7 +278,7 @@ static void gap_t(const void* x, const TDesc& xd, void* y, const TDesc& yd, hipS
       // pixels on a wave's loads per plane are enough (15 x 15 measured equal).  Four
       // lanes per plane bring 64 planes per workgroup; below 32768 planes that is
       // two workgroups per CU or fewer, and 16 lanes with four times as many
-      // are as fast or faster (16 x 1024 of 7 x 7 in fp32 3.2 against 3.4 us).
+      // are as fast or faster (16 x 1024 of 7 x 7 in fp32 3.2 against 3.4 us, with one sum per lane).
       if (HW < 256 && reinterpret_cast<uintptr_t>(x) % 16 == 0) {
         const long long planes = (long long)xd.n * xd.c;
         if (planes >= 32768)

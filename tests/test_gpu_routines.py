@@ -579,6 +579,31 @@ def test_gap_planes_edges(dtype, shape):
     g.close()
 
 
+@pytest.mark.parametrize("shape", [(32, 1024, 15, 17), (33, 1024, 14, 14), (33, 1024, 7, 7), (8, 512, 15, 17)])
+def test_gap_planes_partial_sums(shape):
+    """fp32: as close to the exact mean as 64 partial sums per plane are, on
+    centred planes, where the means nearly cancel.  The error of both is a
+    sum over 4096 planes or more of independent roundings, so their ratio
+    strays from 1 by a few percent; sums of up to 64 pixels one after the
+    other give 1.6 on the largest planes."""
+    n, c, h, w = shape
+    x = np.random.default_rng(23).standard_normal(shape).astype(np.float32)
+    exact = x.astype(np.float64).mean((2, 3)).reshape(-1)
+    part = np.zeros((n * c, 64), np.float32)
+    flat = x.reshape(n * c, h * w)
+    for i in range(0, h * w, 64):
+        part[:, :flat[:, i:i + 64].shape[1]] += flat[:, i:i + 64]
+    while part.shape[1] > 1:
+        part = part[:, 0::2] + part[:, 1::2]
+    ref = part[:, 0] * np.float32(np.float32(1) / np.float32(h * w))
+    g = single_layer_graph("f32", shape, {"type": "gap", "in": [0]}, layouts=["NCHW"])
+    out = from_dev(run_routine(g, 0, to_dev(x, "f32")), "f32").reshape(-1)
+    g.close()
+    ratio = np.linalg.norm(out - exact) / np.linalg.norm(ref.astype(np.float64) - exact)
+    print(shape, f"error / error of 64 partial sums {ratio:.3f}", flush=True)
+    assert ratio <= 1.1
+
+
 @pytest.mark.parametrize("case", [(2, 3, 9, 7, 16, 3, 1, 1), (2, 5, 6, 6, 10, 1, 2, 0), (1, 7, 11, 5, 33, 5, 2, 2)])
 def test_wave_split_nchw_reads_no_neighbour(case):
     """fp32 NCHW: the channels past C that fill a chunk are not the next
