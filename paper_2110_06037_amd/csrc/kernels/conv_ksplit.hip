@@ -324,38 +324,44 @@ void ksplit_pack(const void* w, int kp, size_t row_bytes, void* out) {
       }
 }
 
-// The time of a launch, in us, as a base of 3 plus, per round of 256
-// workgroups, a cost per reduction step (eighths of the 16-element steps for
-// the wave-split tiles, 32-element steps for the LDS tile) and one per tile;
-// the LDS tile's steps also wait for one another.  Coefficients fitted to
-// 151 launches of 16 filter shapes (1x1 and 3x3, 16 to 2048 channels) at 49 to
-// 100352 pixels in NHWC and NC8HW8 (rms error 8 to 16 %).  The LDS tile is taken
-// unless a wave-split tile is expected below 0.85 of it, so the rule costs
-// nothing where the model cannot tell them apart.  The picks took these launches 1.6 times
-// faster than the LDS tile alone in the geometric mean: 128 channels 3x3 at
-// 3 x 23 x 23, 29.4 -> 11.1 us; 512 channels at 7 x 7, 103 -> 12.3 us.
-// In NCHW (red counts the filter's padded channels) the LDS tile gathers
-// element by element, 1.26 us per step (18 launches of 27 to 4608 products), and a
-// wave-split step has four times the loads, 1.65 of its NHWC time.  LDS tile ->
-// pick: 16 channels 3x3/2 at 32 x 32, 10.3 -> 5.1 us; 64 at 2 x 28 x 28, 28.0 -> 9.2; 512
-// at 7 x 7, 188 -> 14.9; 256 at 8 x 14 x 14, 98 -> 39.
-static int ksplit_pick_f32(int layout, long long m, int k, long long red, bool lds_ok) {
+// The time of a launch, in us: a base plus, per round of 256 workgroups, a cost
+// per reduction step and one per tile.  A wave-split tile's step is eight
+// 16-element steps, one per wave, and its rounds are whole; the LDS tile's is 32
+// elements, its later rounds overlap (tiles / 256, at least one), and its steps
+// also wait for one another.  In NCHW both load element by element; a pointwise
+// layer's steps read new lines every time, where taps read those of their
+// neighbours again, and take a wave-split tile up to twice as long.  red counts the
+// channels rounded up to 8.  Fitted to
+// 2147 convolutions, each run on the four kernels: 1x1 to 7x7 at stride 1 and 2, 3 to 512
+// channels to 4 to 512, 4 to 240000 pixels, in the three layouts (rms error 7 to
+// 12 %).  The LDS tile is taken unless a wave-split tile is expected below 0.9 of
+// it.  Against the LDS tile alone the picks are 1.69 (NCHW) and 1.58 times faster in the
+// geometric mean, 0.8 and 1.3 % from the fastest of the four, and of the 2147 one
+// is slower than the LDS tile by more than 3 % (1x1, 80 -> 10 channels, 47526 pixels, 6 %).
+// LDS tile -> pick: 512 channels 3x3 at 7 x 7, 103 -> 12.3 us; in NCHW 16 channels
+// 3x3/2 at 32 x 32, 10.3 -> 5.1; 64 at 2 x 28 x 28, 28.0 -> 9.2.
+static int ksplit_pick_f32(int layout, bool k1, long long m, int k, long long red, bool lds_ok) {
   struct Fit {
     int fm, fn;
-    double step, tile;
+    double base[2], step[2], tile[2];  // taps, pointwise
   };
-  static const Fit fits[] = {{1, 1, 0.333, 0.835}, {2, 1, 0.471, 0.765}, {2, 2, 0.700, 1.358}};
+  static const Fit vec[] = {{1, 1, {3.17, 3.08}, {0.22, 0.38}, {1.35, 0.82}},
+                            {2, 1, {2.87, 2.97}, {0.39, 0.41}, {1.23, 0.99}},
+                            {2, 2, {2.82, 2.71}, {0.61, 0.73}, {2.06, 1.78}}};
+  static const Fit nchw[] = {{1, 1, {3.18, 2.83}, {0.30, 0.63}, {1.57, 1.28}},
+                             {2, 1, {3.96, 3.03}, {0.63, 0.89}, {1.31, 1.68}},
+                             {2, 2, {3.85, 3.27}, {0.87, 1.28}, {2.33, 2.11}}};
   double best = 1e30;
   int pick = 0;
   if (lds_ok) {
     const double r = std::max(1.0, (double)(((m + 63) / 64) * ((k + 63) / 64)) / 256.0), s = (double)((red + 31) / 32);
-    best = layout == NCHW ? 0.85 * (4.0 + r * (1.17 * s + 1.0) + 0.09 * s)
-                          : 0.85 * (3.0 + r * (0.642 * s + 1.039) + 0.09 * s);
+    best = layout == NCHW ? 0.9 * (3.28 + r * (0.84 * s + 0.83) + 0.45 * s)
+                          : 0.9 * (3.11 + r * (0.63 * s + 0.90) + 0.17 * s);
   }
-  const double s = (double)(((red + 15) / 16 + 7) / 8);
-  for (const Fit& f : fits) {
+  const double s = (double)((red + 15) / 16) / 8.0;
+  for (const Fit& f : layout == NCHW ? nchw : vec) {
     const long long wg = ((m + 16 * f.fm - 1) / (16 * f.fm)) * ((k + 16 * f.fn - 1) / (16 * f.fn));
-    const double t = 3.0 + std::max(1.0, (double)wg / 256.0) * (f.step * (layout == NCHW ? 1.65 : 1.0) * s + f.tile);
+    const double t = f.base[k1] + (double)((wg + 255) / 256) * (f.step[k1] * s + f.tile[k1]);
     if (t < best) {
       best = t;
       pick = f.fm * 8 + f.fn;
@@ -382,7 +388,8 @@ bool ksplit_applicable(int dtype, int layout, int n, int c, int h, int w, int r,
 int ksplit_tile_f32(int layout, int n, int c, int h, int w, int r, int s, int stride, int pad, int k, int c2) {
   if (!ksplit_applicable(0, layout, n, c, h, w, r, s, stride, pad, k, c2)) return 0;
   const long long p = (h + 2 * pad - r) / stride + 1, q = (w + 2 * pad - s) / stride + 1;
-  return ksplit_pick_f32(layout, n * p * q, k, (long long)r * s * (layout == NCHW ? (c + 7) / 8 * 8 : c) + c2, !c2);
+  return ksplit_pick_f32(layout, r == 1 && s == 1 && pad == 0, n * p * q, k, (long long)r * s * ((c + 7) / 8 * 8) + c2,
+                         !c2);
 }
 
 template <typename T, int L, int FM, int FN, int NW, int D>
