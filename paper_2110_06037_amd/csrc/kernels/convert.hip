@@ -408,10 +408,18 @@ bool convert_vec16(const void* xv, const TDesc& xd, void* yv, const TDesc& yd, h
   }
   if ((a == NCHW && b == NHWC) || (a == NHWC && b == NCHW)) {
     if (C % 8 != 0 || C <= 8) return false;
-    // up to 32 MiB (what the caches hold of both sides): past that the tensor
-    // streams, and the LDS tile's lane-consecutive runs are 3 to 6 % faster
-    // (51.4 MB to NHWC 18.4 against 19.0 us, back 16.6 against 17.7)
-    if (HW % 4 == 0 && (long long)N * C * HW * 2 <= (1ll << 25)) {
+    // In registers below 32 MiB (what the caches hold of both sides): past that the
+    // tensor streams, and the LDS tile's lane-consecutive runs are 3 to 6 % faster
+    // (51.4 MB to NHWC 18.4 against 19.0 us, back 16.6 against 17.7; 33.5 MB of 256-pixel
+    // planes 11.0 against 12.4).  Where the LDS tile also has 16-byte
+    // pixel vectors (H*W % 8 == 0) only from 3 MiB on: below, both run at the
+    // dispatch's pace, and the tile is 2 to 11 % faster towards NCHW (2.1 MB 2.57
+    // against 2.87 us) and up to 5 % towards NHWC (2.76 against 2.89); from 3.2 MB
+    // registers are (12.8 MB 5.2 against 6.6 us, back 5.4 against 6.5).  Without them the
+    // tile moves single elements, and registers win at every size (3.2 MB of 14 x 14
+    // 2.7 against 3.9 us, back 2.8 against 4.6).
+    const long long bytes = (long long)N * C * HW * 2;
+    if (HW % 4 == 0 && bytes < (1ll << 25) && (HW % 8 != 0 || bytes >= 3ll << 20)) {
       const int G = HW % 8 == 0 ? 8 : 4, CB = C / 8, HWT = (HW + 8 * G - 1) / (8 * G), CBT = (CB + 7) / 8;
       const long long tiles = (long long)N * CBT * HWT;
       if (tiles >= (1ll << 31) - 4) return false;

@@ -241,6 +241,18 @@ def test_add_and_converters_bit_exact(dtype, c, hw):
                 assert np.array_equal(out, ref), ids
 
 
+@pytest.mark.parametrize("shape", [(1, 64, 128, 191), (1, 64, 128, 192), (32, 2048, 16, 16), (1, 2048, 127, 64)])
+def test_converter_size_limits(shape):
+    """NCHW -> NHWC -> NCHW in 16 bits on both sides of the sizes between which
+    planes of a multiple of 8 pixels are transposed in registers (3 MiB, 32 MiB)."""
+    x = random_tensor(shape, "f16", seed=14, dist="int")
+    g = Graph("f16", *shape, device=0, layouts=["NHWC"])
+    g.add_maxpool(0, 1, 1, 0)
+    g.set_path([0, 0])
+    assert np.array_equal(from_dev(g.run(to_dev(x, "f16")), "f16"), to_f64(x, "f16"))
+    g.close()
+
+
 def test_converter_past_the_register_transpose_limit():
     # 34.5 MB of 16-bit values (past the 32 MiB up to which NCHW <-> NHWC
     # transposes in registers): the LDS tile, with a partial channel tile
